@@ -71,7 +71,7 @@ void release_device(etc_plan_t* P) {
   if (P->device < 0) return;
   if (P->static_gen) {  // tables in the static array: nothing to free
     P->d_boxes = nullptr;
-    P->d_route_tensors = nullptr;
+    P->d_cost = nullptr;
     P->d_home = nullptr;
     P->d_failed = nullptr;
     return;
@@ -80,19 +80,19 @@ void release_device(etc_plan_t* P) {
   const bool have_prev = hipGetDevice(&prev) == hipSuccess;
   if (prev != P->device) (void)hipSetDevice(P->device);
   if (P->d_boxes) (void)hipFree(P->d_boxes);
-  if (P->d_route_tensors) (void)hipFree(P->d_route_tensors);
+  if (P->d_cost) (void)hipFree(P->d_cost);
   if (P->d_home) (void)hipFree(P->d_home);
   if (P->d_failed) (void)hipFree(P->d_failed);
   if (have_prev && prev != P->device) (void)hipSetDevice(prev);
   P->d_boxes = nullptr;
-  P->d_route_tensors = nullptr;
+  P->d_cost = nullptr;
   P->d_home = nullptr;
   P->d_failed = nullptr;
 }
 
 int check_device_plan(const etc_plan_t* P) {
   if (!P) return fail(ETC_ERR_INVALID_ARG, "plan is NULL");
-  if (P->device < 0 || !P->d_route_tensors || !P->d_home)
+  if (P->device < 0 || !P->d_cost || !P->d_home)
     return fail(ETC_ERR_INVALID_ARG, "plan was built with ETC_PLAN_HOST_ONLY");
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
@@ -191,6 +191,13 @@ int build_copy_tables(etc_plan_t* P, int rank, std::vector<etc::CopyBox>* all) {
   return ETC_OK;
 }
 
+// The cost kernel's table as it lies in device memory.
+void put_cost_table(const etc_plan_t& P, void* to) {
+  std::memcpy(to, P.cost.groups.data(), P.cost.first_byte());
+  std::memcpy(static_cast<char*>(to) + P.cost.first_byte(), P.cost.first.data(),
+              P.cost.first.size() * sizeof(uint32_t));
+}
+
 int upload(etc_plan_t* P, int rank) {
   using namespace etc;
   hipError_t e = hipGetDevice(&P->device);
@@ -207,14 +214,12 @@ int upload(etc_plan_t* P, int rank) {
     e = hipMemcpy(P->d_boxes, all.data(), all.size() * sizeof(CopyBox), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpy (copy tables)");
   }
-  const size_t rt_bytes = std::max<size_t>(1, P->route_tensors.size()) * sizeof(RouteTensor);
-  e = hipMalloc(&P->d_route_tensors, rt_bytes);
+  e = hipMalloc(&P->d_cost, P->cost.bytes());
   if (e != hipSuccess) return fail(ETC_ERR_NOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
-  if (!P->route_tensors.empty()) {
-    e = hipMemcpy(P->d_route_tensors, P->route_tensors.data(),
-                  P->route_tensors.size() * sizeof(RouteTensor), hipMemcpyHostToDevice);
-    if (e != hipSuccess) return hip_fail(e, "hipMemcpy (tensor table)");
-  }
+  std::vector<char> cost(P->cost.bytes());
+  put_cost_table(*P, cost.data());
+  e = hipMemcpy(P->d_cost, cost.data(), cost.size(), hipMemcpyHostToDevice);
+  if (e != hipSuccess) return hip_fail(e, "hipMemcpy (tensor groups)");
   e = hipMalloc(&P->d_home, std::max<size_t>(1, P->home.size()) * sizeof(int32_t));
   if (e != hipSuccess) return fail(ETC_ERR_NOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
   e = hipMemcpy(P->d_home, P->home.data(), P->home.size() * sizeof(int32_t), hipMemcpyHostToDevice);
@@ -230,7 +235,7 @@ int upload(etc_plan_t* P, int rank) {
 }
 
 // The same device tables written into the current device's static array:
-// copy boxes, tensor table, pairing, failed ranks, each at a multiple of 256
+// copy boxes, tensor groups, pairing, failed ranks, each at a multiple of 256
 // bytes.  No device memory is allocated.
 int upload_static(etc_plan_t* P, int rank) {
   using namespace etc;
@@ -241,8 +246,10 @@ int upload_static(etc_plan_t* P, int rank) {
   int rc = build_copy_tables(P, rank, &all);
   if (rc) return rc;
   auto up = [](size_t n) { return (n + 255) / 256 * 256; };
-  const size_t o_rt = up(all.size() * sizeof(CopyBox));
-  const size_t o_home = o_rt + up(P->route_tensors.size() * sizeof(RouteTensor));
+  const size_t o_cg = up(all.size() * sizeof(CopyBox));
+  // the tensor groups' room is counted as one RouteTensor per tensor, more
+  // than they need: which plans fit the array does not depend on the grouping
+  const size_t o_home = o_cg + up(std::max(P->route_tensors.size() * sizeof(RouteTensor), P->cost.bytes()));
   const size_t o_failed = o_home + up(P->home.size() * sizeof(int32_t));
   const size_t total = o_failed + P->failed_bits.size() * sizeof(uint32_t);
   if (total > size_t(ETC_STATIC_TABLE_BYTES))
@@ -252,7 +259,7 @@ int upload_static(etc_plan_t* P, int rank) {
                                          " (ETC_STATIC_TABLE_BYTES); use etc_plan, or a plan per process");
   std::vector<unsigned char> img(std::max<size_t>(total, 1), 0);
   std::memcpy(img.data(), all.data(), all.size() * sizeof(CopyBox));
-  std::memcpy(img.data() + o_rt, P->route_tensors.data(), P->route_tensors.size() * sizeof(RouteTensor));
+  put_cost_table(*P, img.data() + o_cg);
   std::memcpy(img.data() + o_home, P->home.data(), P->home.size() * sizeof(int32_t));
   std::memcpy(img.data() + o_failed, P->failed_bits.data(), P->failed_bits.size() * sizeof(uint32_t));
   std::unique_lock<std::shared_mutex> lock(g_static_mu);
@@ -267,7 +274,7 @@ int upload_static(etc_plan_t* P, int rank) {
   P->device = dev;
   P->static_gen = slot->gen;
   P->d_boxes = all.empty() ? nullptr : reinterpret_cast<CopyBox*>(base);
-  P->d_route_tensors = reinterpret_cast<RouteTensor*>(base + o_rt);
+  P->d_cost = reinterpret_cast<char*>(base + o_cg);
   P->d_home = reinterpret_cast<int32_t*>(base + o_home);
   P->d_failed = P->failed_bits.empty() ? nullptr : reinterpret_cast<uint32_t*>(base + o_failed);
   return ETC_OK;
@@ -381,6 +388,7 @@ int make_plan(const etc_model_desc* model, const etc_parallel_cfg* src, const et
     }
     P->tensors = etc::build_tensor_table(P->model);
     etc::build_route_tensors(*P);
+    P->cost = etc::build_cost_table(*P);
     P->home.assign(D, -1);
     if (flags & ETC_PLAN_SKETCH) {
       etc::sketch_pairing(*P, dead);
@@ -598,8 +606,9 @@ int etc_cost_matrix(const etc_plan_t* P, int which, uint64_t* d_out, void* strea
     return fail(ETC_ERR_UNSUPPORTED, "a cost matrix is limited to 2^31 - 1 cells");
   const etc::RouteCtx ctx{P->src.tp, P->src.pp, P->src.dp, P->dst.tp, P->dst.pp, P->dst.dp,
                          P->d_failed};
-  hipError_t e = etc::launch_cost(P->d_route_tensors, int(P->route_tensors.size()), P->d_home, ctx,
-                                  which, d_out, static_cast<hipStream_t>(stream));
+  hipError_t e = etc::launch_cost(reinterpret_cast<const etc::CostGroup*>(P->d_cost),
+                                  reinterpret_cast<const uint32_t*>(P->d_cost + P->cost.first_byte()), P->d_home,
+                                  ctx, etc::lcm_slices(*P), which, d_out, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "cost matrix launch");
   return ETC_OK;
 }

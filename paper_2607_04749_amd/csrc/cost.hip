@@ -1,13 +1,25 @@
 // cost.hip -- byte-overlap / routing / cost matrices over every (source,
 // target) rank pair, on the GPU (Sec. III-B cost matrix, Sec. III-C LCM
-// workload items).  Two or four 64-wide wavefronts per matrix cell; their
-// lanes stride over the logical tensors, each evaluating the interval form of
-// the routing rule (route.hpp) for one tensor; the 64-bit partial sums are
-// reduced with lane shuffles, then across the cell's wavefronts in LDS.
-// Integer work on a few KB of tables: latency bound, microseconds.
+// workload items).  In LCM slices a pair of shards overlaps alike in every
+// split tensor, so a cell needs only the tensors' summed sizes per pair of
+// stages: a loop over the CostGroups of its target stage (two or three for the
+// 70B model's 563 tensors) and one product.  Cells that the rules make empty
+// or infinite (most of a data-parallel job's) skip the loop.
 // COST is ETC_COST_INF between ranks of different data-parallel replicas and
 // towards failed ranks (Sec. III-C); a failed rank holds and sends nothing.
+//
+// Integer work on a few hundred bytes of tables: launch latency for a single
+// replica's ranks.  For 1024 x 768 cells the integer divisions that turn ranks
+// into grid coordinates took longest, so a workgroup covers a tile of the
+// matrix: a thread stays in one column and the rows' coordinates are worked
+// out once per workgroup.  Llama-70B, MI355X, kernel time, against two
+// wavefronts per cell that looped over the 563 tensors:
+//   64 x 32 cells       COST 3.7 us, ROUTE 5.4 us    (6.6 to 8.5 us)
+//   1024 x 768 cells    COST 5.0 us, ROUTE 7.8 us, 11.5 us where a node of
+//                       8 ranks was lost             (1030 to 1360 us)
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "etc_internal.hpp"
 #include "route.hpp"
@@ -16,92 +28,127 @@ namespace etc {
 
 namespace {
 
-constexpr int kWave = 64;  // wavefront width on CDNA
+constexpr int kCmThreads = 256;
+constexpr int kCmRows = 32;    // rows of a workgroup's tile, at most
 
-// Sum of v over the 64 lanes of a wavefront (every lane gets the total).
-__device__ __forceinline__ uint64_t wave_sum(uint64_t v) {
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+// A workgroup's tile: 1 << wbits columns by `rows` rows, kCmThreads >> wbits
+// of them at a time.
+struct CostTile {
+  uint32_t wbits, rows, across;  // across: tiles side by side
+};
+
+// Whether a rank of [lo, lo + n) failed.
+__device__ inline bool any_dead(const RouteCtx& c, int lo, int n) {
+  if (c.failed == nullptr) return false;
+  const int hi = lo + n;
+  uint32_t found = 0;
+  for (int w = lo >> 5; w <= (hi - 1) >> 5; ++w) {
+    uint32_t bits = c.failed[w];
+    if (w == lo >> 5) bits &= ~0u << (lo & 31);
+    if (w == (hi - 1) >> 5) bits &= ~0u >> (31 - ((hi - 1) & 31));
+    found |= bits;
+  }
+  return found != 0;
 }
 
-// kWaves wavefronts per matrix cell, kCmThreads / (64 * kWaves) cells per
-// workgroup.  Each wavefront reduces with lane shuffles; the wavefronts of a
-// cell then add up in LDS after one barrier.
-template <int kWaves>
-__global__ __launch_bounds__(kCmThreads) void cost_kernel(const RouteTensor* __restrict__ T,
-                                                          int nt, const int32_t* __restrict__ home,
-                                                          RouteCtx c, int which,
-                                                          uint64_t* __restrict__ out) {
-  constexpr int kCellThreads = kWave * kWaves;
-  constexpr int kCellsPerBlock = kCmThreads / kCellThreads;
-  __shared__ uint64_t part[2][kCmThreads / kWave];
+template <int kWhich>
+__global__ __launch_bounds__(kCmThreads) void cost_kernel(const CostGroup* __restrict__ groups,
+                                                          const uint32_t* __restrict__ first,
+                                                          const int32_t* __restrict__ home, RouteCtx c,
+                                                          LcmSlices lcm, CostTile tile, uint64_t* __restrict__ out) {
+  constexpr bool kCost = kWhich == ETC_CM_COST;  // rows are targets; sources otherwise
+  __shared__ SourceAt row_src[kCmRows];
+  __shared__ TargetAt row_dst[kCmRows];
   const int S = c.tps * c.pps * c.dps, D = c.tpd * c.ppd * c.dpd;
-  const int ct = int(threadIdx.x) % kCellThreads;
-  const int cell = int(blockIdx.x) * kCellsPerBlock + int(threadIdx.x) / kCellThreads;
-  const bool live = cell < S * D;  // every thread reaches the barrier below
-  const int cc = live ? cell : 0;
-  const int s = cc / D, d = cc % D;
-  const int pp_d = (d % (c.tpd * c.ppd)) / c.tpd, tp_d = d % c.tpd;
-  const int pp_s = (s % (c.tps * c.pps)) / c.tps, tp_s = s % c.tps;
-  const int rep_s = s / (c.tps * c.pps), rep_d = d / (c.tpd * c.ppd);
-  const bool dead = rank_dead(c, s);
-  const int home_d = home[d];
-  uint64_t val = 0, need = 0;
-  for (int i = ct; live && i < nt; i += kCellThreads) {
-    const RouteTensor t = T[i];
-    if (role_on(t.dst_stage, pp_d) < 0) continue;
-    const int64_t unit = unit_elems(t);
-    const Span want = shard_span(t, tp_d, c.tpd);
-    need += uint64_t(want.len() * unit);
-    if (which == ETC_CM_ROUTE) {
-      val += uint64_t(routed_span(t, s, d, home_d, c).len() * unit);
-    } else {
-      if (dead || role_on(t.src_stage, pp_s) < 0) continue;  // a failed rank holds nothing
-      if (which == ETC_CM_OVERLAP_SHARDED && (!t.single_copy || rep_s != rep_d % c.dps)) continue;
-      const Span have = shard_span(t, tp_s, c.tps);
-      const Span x{have.lo > want.lo ? have.lo : want.lo, have.hi < want.hi ? have.hi : want.hi};
-      val += uint64_t(x.len() * unit);
-    }
-  }
-  val = wave_sum(val);
-  need = wave_sum(need);
-  const int w = int(threadIdx.x) / kWave;
-  if (int(threadIdx.x) % kWave == 0) {
-    part[0][w] = val;
-    part[1][w] = need;
+  const uint32_t nrow = uint32_t(kCost ? D : S), ncol = uint32_t(kCost ? S : D);
+  const uint32_t band = blockIdx.x / tile.across, row0 = band * tile.rows;
+  const uint32_t col = ((blockIdx.x - band * tile.across) << tile.wbits) + (threadIdx.x & ((1u << tile.wbits) - 1));
+  const uint32_t sub = threadIdx.x >> tile.wbits, step = kCmThreads >> tile.wbits;
+  const int mine = int(col < ncol ? col : 0);
+  // the column's coordinates stay in registers, the rows' in LDS
+  SourceAt a{};
+  TargetAt b{};
+  bool lost = false;  // ROUTE: the replica that serves the target lost a rank
+  if (kCost) {
+    a = source_at(mine, c);
+    if (threadIdx.x < tile.rows && row0 + threadIdx.x < nrow)
+      row_dst[threadIdx.x] = target_at(int(row0 + threadIdx.x), -1, c);
+  } else {
+    b = target_at(mine, kWhich == ETC_CM_ROUTE ? home[mine] : -1, c);
+    if (kWhich == ETC_CM_ROUTE) lost = any_dead(c, b.rep0 * c.tps * c.pps, c.tps * c.pps);
+    if (threadIdx.x < tile.rows && row0 + threadIdx.x < nrow)
+      row_src[threadIdx.x] = source_at(int(row0 + threadIdx.x), c);
   }
   __syncthreads();
-  if (live && ct == 0) {
-    val = 0;
-    need = 0;
-    for (int j = 0; j < kWaves; ++j) {
-      val += part[0][w + j];
-      need += part[1][w + j];
+  for (uint32_t r = sub; r < tile.rows; r += step) {
+    const uint32_t row = row0 + r;
+    if (row >= nrow || col >= ncol) break;
+    if (kCost) b = row_dst[r];
+    else a = row_src[r];
+    bool held = !a.dead;  // whether the cell needs the loop over the groups
+    if (kCost) held = held && a.rep == b.rep;
+    if (kWhich == ETC_CM_OVERLAP_SHARDED) held = held && a.rep == b.rep0;
+    // a replica beyond the serving one stands in only where that one lost a rank
+    if (kWhich == ETC_CM_ROUTE) held = held && (a.rep == b.rep0 || a.s == b.home || lost);
+    // elements of a slice / of whole tensors: moved or shared, and needed by the target
+    uint64_t slice = 0, whole = 0, need_slice = 0, need_whole = 0;
+    if (held) {
+      const uint32_t end = first[b.pp + 1];
+      for (uint32_t i = first[b.pp]; i < end; ++i) {
+        const CostGroup& g = groups[i];
+        if (kCost) {
+          need_slice += g.slice;
+          need_whole += g.whole;
+        }
+        if (role_on(g.src_stage, a.pp) < 0) continue;
+        if (kWhich == ETC_CM_ROUTE) {
+          if (sends_shard(a, b, g.src_stage, false, g.role_d, c)) slice += g.slice;
+          if (sends_shard(a, b, g.src_stage, true, g.role_d, c)) whole += g.whole;
+        } else if (kWhich == ETC_CM_OVERLAP_SHARDED) {
+          slice += g.slice1;
+          whole += g.whole1;
+        } else {
+          slice += g.slice;
+          whole += g.whole;
+        }
+      }
     }
+    const int64_t s0 = a.tp * lcm.src, d0 = b.tp * lcm.dst;  // first LCM slice of each shard
+    const Span x{s0 > d0 ? s0 : d0, s0 + lcm.src < d0 + lcm.dst ? s0 + lcm.src : d0 + lcm.dst};
     constexpr uint64_t kBytesPerElem = 14;  // 2 (bf16) + 4 + 4 + 4 (fp32)
-    if (which == ETC_CM_COST)
-      out[size_t(d) * S + s] = (dead || rep_s != rep_d) ? uint64_t(ETC_COST_INF)
-                                                        : (need - val) * kBytesPerElem;
-    else
-      out[size_t(s) * D + d] = val * kBytesPerElem;
+    uint64_t bytes = (uint64_t(x.len()) * slice + whole) * kBytesPerElem;
+    if (kCost)
+      bytes = held ? (uint64_t(lcm.dst) * need_slice + need_whole) * kBytesPerElem - bytes : uint64_t(ETC_COST_INF);
+    out[size_t(row) * ncol + col] = bytes;
   }
 }
 
 }  // namespace
 
-hipError_t launch_cost(const RouteTensor* rt, int nt, const int32_t* home, RouteCtx ctx,
-                       int which, uint64_t* out, hipStream_t stream) {
-  const unsigned cells = unsigned(ctx.tps * ctx.pps * ctx.dps) * unsigned(ctx.tpd * ctx.ppd * ctx.dpd);
-  // few cells: 4 wavefronts each, so the tensor loop is short; many cells:
-  // 2 each, which measured faster on MI355X at 2048 cells
-  if (cells <= 1024) {
-    hipLaunchKernelGGL(cost_kernel<4>, dim3(cells), dim3(kCmThreads), 0, stream, rt, nt, home,
-                       ctx, which, out);
-  } else {
-    hipLaunchKernelGGL(cost_kernel<2>, dim3((cells + 1) / 2), dim3(kCmThreads), 0, stream, rt, nt,
-                       home, ctx, which, out);
+hipError_t launch_cost(const CostGroup* groups, const uint32_t* first, const int32_t* home, RouteCtx ctx,
+                       LcmSlices lcm, int which, uint64_t* out, hipStream_t stream) {
+  const uint32_t S = uint32_t(ctx.tps * ctx.pps * ctx.dps), D = uint32_t(ctx.tpd * ctx.ppd * ctx.dpd);
+  const uint32_t nrow = which == ETC_CM_COST ? D : S, ncol = which == ETC_CM_COST ? S : D;
+  CostTile tile{0, 0, 0};
+  while (tile.wbits < 8 && (1u << tile.wbits) < ncol) ++tile.wbits;
+  tile.across = (ncol + (1u << tile.wbits) - 1) >> tile.wbits;
+  // One pass of rows per workgroup, more only while 1024 workgroups are left:
+  // rows of a thread follow each other, so at 1024 x 768 cells two rows took
+  // 5.0 us (COST) and 11.5 us (ROUTE), one row 5.6 and 11.2, four 5.6 and 14.9.
+  const uint32_t pass = std::min<uint32_t>(kCmThreads >> tile.wbits, kCmRows);
+  tile.rows = pass;
+  while (tile.rows * 2 <= kCmRows && uint64_t((nrow + 2 * tile.rows - 1) / (2 * tile.rows)) * tile.across >= 1024)
+    tile.rows *= 2;
+  const dim3 grid((nrow + tile.rows - 1) / tile.rows * tile.across), block(kCmThreads);
+#define ETC_COST(W) \
+  hipLaunchKernelGGL(cost_kernel<W>, grid, block, 0, stream, groups, first, home, ctx, lcm, tile, out)
+  switch (which) {
+    case ETC_CM_ROUTE: ETC_COST(ETC_CM_ROUTE); break;
+    case ETC_CM_OVERLAP: ETC_COST(ETC_CM_OVERLAP); break;
+    case ETC_CM_OVERLAP_SHARDED: ETC_COST(ETC_CM_OVERLAP_SHARDED); break;
+    default: ETC_COST(ETC_CM_COST); break;
   }
+#undef ETC_COST
   return hipGetLastError();
 }
 

@@ -66,6 +66,29 @@ struct RouteTensor {
   int32_t single_copy;   // exactly one copy in both grids
 };
 
+// What the cost kernel reads in place of the tensors: all tensors that a
+// target stage holds in copy role role_d and whose roles lie on the same source
+// stages, summed.  A split dim divides by both TP degrees, hence by their
+// least common multiple, so a pair of shards of any split tensor overlaps in
+// the same number of LCM slices (Sec. III-C) and the tensors' slices add up;
+// replicated tensors count whole.
+struct CostGroup {
+  int32_t src_stage[2];  // as in RouteTensor
+  int32_t role_d, stage_d;
+  uint64_t slice, whole;    // elements: one LCM slice of the split tensors; the replicated ones
+  uint64_t slice1, whole1;  // the same over single-copy tensors
+};
+static_assert(sizeof(CostGroup) == 48, "CostGroup layout");
+
+// The groups by target stage, and for every target stage the index of its
+// first group (one more entry ends the last stage's).
+struct CostTable {
+  std::vector<CostGroup> groups;
+  std::vector<uint32_t> first;
+  size_t first_byte() const { return groups.size() * sizeof(CostGroup); }  // the groups, then `first`
+  size_t bytes() const { return first_byte() + first.size() * sizeof(uint32_t); }
+};
+
 // Launch table of one rank's pack or unpack.
 struct CopyTable {
   bool built = false;
@@ -76,8 +99,6 @@ struct CopyTable {
   std::vector<int32_t> peers;  // rank of each peer slot (pack: targets, unpack: sources)
 };
 
-constexpr int kCmThreads = 256;
-
 // Routing context of a plan: both grids and the failed source ranks (bitmap,
 // nullptr when none).  Device copies point at device memory.
 struct RouteCtx {
@@ -85,8 +106,13 @@ struct RouteCtx {
   const uint32_t* failed;
 };
 
-hipError_t launch_cost(const RouteTensor* rt, int nt, const int32_t* home, RouteCtx ctx,
-                       int which, uint64_t* out, hipStream_t stream);
+// LCM slices of one shard in the source and the target grid
+struct LcmSlices {
+  int64_t src, dst;
+};
+
+hipError_t launch_cost(const CostGroup* groups, const uint32_t* first, const int32_t* home, RouteCtx ctx,
+                       LcmSlices lcm, int which, uint64_t* out, hipStream_t stream);
 
 }  // namespace etc
 
@@ -98,6 +124,7 @@ struct etc_plan_s {
   uint32_t flags = 0;
   std::vector<etc::LogicalTensor> tensors;
   std::vector<etc::RouteTensor> route_tensors;
+  etc::CostTable cost;  // route_tensors summed for the cost kernel
   // layouts of the ranks of one data-parallel replica: every replica has the
   // same (rank r's layout is that of r mod replica size)
   std::vector<etc::RankLayout> src_layout, dst_layout;
@@ -150,7 +177,7 @@ struct etc_plan_s {
   // non-zero: the device tables live in the library's static array of that
   // device (etc_plan_static), written by its static_gen-th call there
   uint64_t static_gen = 0;
-  etc::RouteTensor* d_route_tensors = nullptr;
+  char* d_cost = nullptr;  // device copy of cost: groups, then first
   int32_t* d_home = nullptr;  // device copy of home (D entries)
   uint32_t* d_failed = nullptr;  // device copy of failed_bits
   etc::CopyBox* d_boxes = nullptr;

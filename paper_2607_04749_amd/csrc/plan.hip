@@ -3,7 +3,9 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cstring>
+#include <map>
 #include <numeric>
 #include <stdexcept>
 #include <string>
@@ -349,6 +351,37 @@ void build_route_tensors(etc_plan_t& P) {
     }
     r.single_copy = copies_src == 1 && copies_dst == 1;
   }
+}
+
+LcmSlices lcm_slices(const etc_plan_t& P) {
+  const int64_t l = std::lcm(int64_t(P.src.tp), int64_t(P.dst.tp));
+  return LcmSlices{l / P.src.tp, l / P.dst.tp};
+}
+
+CostTable build_cost_table(const etc_plan_t& P) {
+  const int64_t lcm = std::lcm(int64_t(P.src.tp), int64_t(P.dst.tp));
+  // by target stage, then target role and source stages
+  std::map<std::array<int32_t, 4>, CostGroup> sums;
+  for (const RouteTensor& t : P.route_tensors)
+    for (int role = 0; role < 2; ++role) {
+      if (t.dst_stage[role] < 0) continue;
+      CostGroup& g = sums[{t.dst_stage[role], role, t.src_stage[0], t.src_stage[1]}];
+      const uint64_t n = t.split == kRepl ? uint64_t(unit_elems(t)) : uint64_t(split_extent(t) / lcm * unit_elems(t));
+      (t.split == kRepl ? g.whole : g.slice) += n;
+      if (t.single_copy) (t.split == kRepl ? g.whole1 : g.slice1) += n;
+    }
+  CostTable c;
+  c.first.assign(size_t(P.dst.pp) + 1, 0);
+  for (auto& [key, g] : sums) {
+    g.stage_d = key[0];
+    g.role_d = key[1];
+    g.src_stage[0] = key[2];
+    g.src_stage[1] = key[3];
+    c.groups.push_back(g);
+    ++c.first[size_t(g.stage_d) + 1];
+  }
+  for (size_t i = 1; i < c.first.size(); ++i) c.first[i] += c.first[i - 1];
+  return c;
 }
 
 RouteCtx host_route_ctx(const etc_plan_t& P) {

@@ -22,6 +22,9 @@ RankLayout build_layout(const std::vector<LogicalTensor>& T, const Grid& g, int 
 void validate(const etc_model_desc& m, const etc_parallel_cfg& src, const etc_parallel_cfg& dst);
 // per-tensor routing records (stages per copy role, single-copy flag)
 void build_route_tensors(etc_plan_t& P);
+// the tensors summed by their stages, for the cost matrices
+CostTable build_cost_table(const etc_plan_t& P);
+LcmSlices lcm_slices(const etc_plan_t& P);
 // routing context of a plan's host tables
 RouteCtx host_route_ctx(const etc_plan_t& P);
 // COST of one replica pair on the host (rows: a replica's target ranks)

@@ -59,64 +59,94 @@ __host__ __device__ inline bool rank_dead(const RouteCtx& c, int s) {
   return c.failed != nullptr && ((c.failed[s >> 5] >> (s & 31)) & 1u);
 }
 
-// Range of the split dim that source s sends to target d for tensor t (empty
-// when s sends nothing).  home is the source rank paired with d in the
-// migration sketch (the same GPU), or -1.  Rules (Sec. III-D, Sec. III-C):
+// Grid coordinates of a source rank.
+struct SourceAt {
+  int s, pp, tp, rep;
+  bool dead;  // failed: it holds and sends nothing
+};
+__host__ __device__ inline SourceAt source_at(int s, const RouteCtx& c) {
+  const int pt = c.tps * c.pps, rep = s / pt, r = s - rep * pt, pp = r / c.tps;
+  return SourceAt{s, pp, r - pp * c.tps, rep, rank_dead(c, s)};
+}
+
+// Grid coordinates of a target rank, and of home, the source rank paired with
+// it in the migration sketch (the same GPU), or -1.
+struct TargetAt {
+  int pp, tp, rep;
+  int rep0;              // source replica that serves d's replica
+  int tp_mod;            // tp mod TP_src
+  int home, pp_h, tp_h;  // pp_h = -2, no stage, without a home
+};
+__host__ __device__ inline TargetAt target_at(int d, int home, const RouteCtx& c) {
+  const int pt = c.tpd * c.ppd, rep = d / pt, r = d - rep * pt, pp = r / c.tpd, tp = r - pp * c.tpd;
+  TargetAt t{pp, tp, rep, rep % c.dps, tp % c.tps, home, -2, 0};
+  if (home >= 0) {
+    t.pp_h = home / c.tps % c.pps;
+    t.tp_h = home % c.tps;
+  }
+  return t;
+}
+
+// Whether live source a, which holds a tensor's shard (the whole tensor if
+// `repl`), is the one that sends what target b needs of it.  src_stage: the stages
+// of the tensor's copy roles in the source grid; role_d: the copy role that b
+// holds.  Rules (Sec. III-D, Sec. III-C):
 //  - data the paired source already holds stays with it (Refer);
 //  - otherwise target replica j is served by source replica j mod DP_src (kept
 //    replicas stay, scale-out replicas are fed round-robin), and within it by
 //    the live holder with the smallest key_less key;
 //  - if no live rank of that replica holds the data, the next replicas in
 //    order stand in (fault tolerance through DP replicas).
-// A failed rank sends nothing.  Data with no live holder is routed nowhere;
-// the planner reports it as unrecoverable.
-__host__ __device__ inline Span routed_span(const RouteTensor& t, int s, int d, int home,
-                                            const RouteCtx& c) {
-  const Span none{0, 0};
-  const int rd = d % (c.tpd * c.ppd);
-  const int pp_d = rd / c.tpd, tp_d = rd % c.tpd, rep_d = d / (c.tpd * c.ppd);
-  const int role_d = role_on(t.dst_stage, pp_d);
-  if (role_d < 0) return none;
-  const int pt = c.tps * c.pps;
-  const int pp_s = (s % pt) / c.tps, tp_s = s % c.tps;
-  if (rank_dead(c, s) || role_on(t.src_stage, pp_s) < 0) return none;
-  const Span need = shard_span(t, tp_d, c.tpd);
-  const Span have = shard_span(t, tp_s, c.tps);
-  const Span x{have.lo > need.lo ? have.lo : need.lo, have.hi < need.hi ? have.hi : need.hi};
-  if (x.len() == 0) return none;
-  if (s == home) return x;
-  if (home >= 0) {  // does the paired source hold this range?  Then it keeps it.
-    const int pp_x = (home % pt) / c.tps, tp_x = home % c.tps;
-    if (role_on(t.src_stage, pp_x) >= 0) {
-      const Span hx = shard_span(t, tp_x, c.tps);
-      if (hx.lo == have.lo && hx.hi == have.hi) return none;
-    }
-  }
-  // Holders of `have` in a replica: per copy role, the rank on that role's
+// Data with no live holder is routed nowhere; the planner reports it as
+// unrecoverable.
+__host__ __device__ inline bool sends_shard(const SourceAt& a, const TargetAt& b, const int32_t src_stage[2],
+                                            bool repl, int role_d, const RouteCtx& c) {
+  if (a.s == b.home) return true;
+  // does the paired source hold this shard?  Then it keeps it.
+  if (role_on(src_stage, b.pp_h) >= 0 && (repl || b.tp_h == a.tp)) return false;
+  // Holders of the shard in a replica: per copy role, the rank on that role's
   // stage (any TP rank for a replicated tensor); the first replica in serving
   // order with a live holder decides.
-  const int tpd_mod = tp_d % c.tps;
-  const int r0 = rep_d % c.dps;
-  for (int step = 0; step < c.dps; ++step) {
-    const int rep = (r0 + step) % c.dps;
+  const int pt = c.tps * c.pps;
+  for (int step = 0, rep = b.rep0; step < c.dps; ++step, rep = rep + 1 == c.dps ? 0 : rep + 1) {
+    // the holder with the smallest possible key, when it is alive
+    const int pref = rep * pt + (src_stage[role_d] >= 0 ? src_stage[role_d] : src_stage[1 - role_d]) * c.tps +
+                     (repl ? b.tp_mod : a.tp);
+    if (!rank_dead(c, pref)) return pref == a.s;
     int best_role = -1, best_tp = 0, best_pp = 0;
     for (int r = 0; r < 2; ++r) {
-      const int st = t.src_stage[r];
+      const int st = src_stage[r];
       if (st < 0) continue;
-      const int tp_lo = t.split == kRepl ? 0 : tp_s;
-      const int tp_hi = t.split == kRepl ? c.tps : tp_s + 1;
+      const int tp_lo = repl ? 0 : a.tp;
+      const int tp_hi = repl ? c.tps : a.tp + 1;
       for (int tp = tp_lo; tp < tp_hi; ++tp) {
         if (rank_dead(c, rep * pt + st * c.tps + tp)) continue;
-        if (best_role < 0 || key_less(r, tp, st, best_role, best_tp, best_pp, role_d, tpd_mod)) {
+        if (best_role < 0 || key_less(r, tp, st, best_role, best_tp, best_pp, role_d, b.tp_mod)) {
           best_role = r;
           best_tp = tp;
           best_pp = st;
         }
       }
     }
-    if (best_role >= 0) return (rep * pt + best_pp * c.tps + best_tp == s) ? x : none;
+    if (best_role >= 0) return rep * pt + best_pp * c.tps + best_tp == a.s;
   }
-  return none;
+  return false;
+}
+
+// Range of the split dim that source s sends to target d for tensor t (empty
+// when s sends nothing).
+__host__ __device__ inline Span routed_span(const RouteTensor& t, int s, int d, int home,
+                                            const RouteCtx& c) {
+  const Span none{0, 0};
+  const SourceAt a = source_at(s, c);
+  const TargetAt b = target_at(d, home, c);
+  const int role_d = role_on(t.dst_stage, b.pp);
+  if (role_d < 0 || a.dead || role_on(t.src_stage, a.pp) < 0) return none;
+  const Span need = shard_span(t, b.tp, c.tpd);
+  const Span have = shard_span(t, a.tp, c.tps);
+  const Span x{have.lo > need.lo ? have.lo : need.lo, have.hi < need.hi ? have.hi : need.hi};
+  if (x.len() == 0 || !sends_shard(a, b, t.src_stage, t.split == kRepl, role_d, c)) return none;
+  return x;
 }
 
 }  // namespace etc
