@@ -25,6 +25,20 @@
 // the persistent grid lost about 10 % to an unfavourable relative placement
 // of the source and target buffers.  Loads and stores are non-temporal since
 // nothing is reused.
+//
+// Rows that are not whole aligned vectors (widths that no power of two
+// divides, or an odd tensor ahead of a box in its message) move in windows of
+// the target's 16-byte units (copy_window): unaligned vector loads, aligned
+// vector stores.  A copy of four streams with one 16-byte vector per lane ran
+// at 6.5 TB/s where both sides start on 128-byte lines, 6.0 where the source
+// does not, 5.4 where the target does not start on 64 bytes and 5.1 where
+// neither does: a line that two workgroups share is fetched, or merged into
+// memory, twice, as neighbouring workgroups lie on different XCDs.  With four
+// consecutive KB per XCD (xcd_run) these became 6.25, 5.85 and 5.7, so boxes
+// off the lines take their sub-chunks in that order; boxes on them do not,
+// which would cost 1.7 %.  Against element-by-element copies, in one process:
+// a 1.9 B GPT from TP4 to TP6 (rows of 597 elements) 940 -> 850 us, other
+// shapes with odd widths 9 to 17 % less time, one kind at a time 10 to 12 %.
 #include <hip/hip_runtime.h>
 
 #include "copy_desc.hpp"
@@ -36,120 +50,181 @@ namespace etc {
 namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));  // any element's address
 
 struct CopyArgs {
   const CopyBox* boxes;  // nbox boxes + 1 sentinel (tile0 = ntiles)
   uint32_t nbox;
   uint32_t ntiles;
-  uint32_t kind_mask;  // kinds to copy (bit k)
+  int32_t kind;        // the kind to copy (one-kind launches)
   uint32_t mode;       // MsgMode: what peer[] points at
   char* arena[4];
   char* peer[ETC_MAX_PEERS];  // start of each peer's message (kMsgArenas: source arena of kind k)
 };
 
 // One kind of one tile: where the copy reads and writes, and the row pitches.
-template <bool kPack, int kKind>
+template <bool kPack, int kEs>
 struct KindTile {
-  static constexpr int es = kKind == 0 ? 2 : 4;
-  using E = typename std::conditional<es == 2, uint16_t, uint32_t>::type;
+  using E = typename std::conditional<kEs == 2, uint16_t, uint32_t>::type;
   char* Mb;  // this kind's section of the message, or (Refer) the source arena of this kind
   const char* src;
   char* dst;
   uint64_t sld, dld;  // row pitches in bytes
-  __device__ __forceinline__ KindTile(const CopyArgs& a, const CopyBox& b, char* mbase, const TileGeom& g) {
-    char* A = a.arena[kKind] + tile_arena_elem(b, g) * es;
-    Mb = a.mode == kMsgArenas ? a.peer[kKind]
-                              : mbase + (a.mode == kMsgSections ? section_byte(b.msg_npad, kKind) : 0);
-    char* M = Mb + tile_msg_elem(b, g) * es;
+  __device__ __forceinline__ KindTile(const CopyArgs& a, const CopyBox& b, char* mbase, const TileGeom& g, int kind) {
+    char* A = a.arena[kind] + tile_arena_elem(b, g) * kEs;
+    Mb = a.mode == kMsgArenas ? a.peer[kind]
+                              : mbase + (a.mode == kMsgSections ? section_byte(b.msg_npad, kind) : 0);
+    char* M = Mb + tile_msg_elem(b, g) * kEs;
     src = kPack ? A : M;
     dst = kPack ? M : A;
-    sld = (kPack ? uint64_t(b.a_ld) : b.m_ld) * es;
-    dld = (kPack ? b.m_ld : uint64_t(b.a_ld)) * es;
+    sld = (kPack ? uint64_t(b.a_ld) : b.m_ld) * kEs;
+    dld = (kPack ? b.m_ld : uint64_t(b.a_ld)) * kEs;
   }
   // zero the padding that rounds the box up to a multiple of 8 elements
   __device__ __forceinline__ void zero_pad(const CopyBox& b) const {
-    E* tail = reinterpret_cast<E*>(Mb + (b.m_off + uint64_t(b.rows) * b.cols) * es);
+    E* tail = reinterpret_cast<E*>(Mb + (b.m_off + uint64_t(b.rows) * b.cols) * kEs);
     if (threadIdx.x < b.pad) tail[threadIdx.x] = 0;
   }
 };
 
+// Window w of a row of nc elements.  The first and last window of a row move
+// as up to three pieces of 4, 2 and 1 elements, each aligned on the target
+// side.  All of a wavefront's loads are issued before any store: most
+// wavefronts hold an end of some row, and a second load after the first
+// store would double their time.
+template <int kEs>
+__device__ __forceinline__ void copy_window(const char* src, char* dst, uint32_t w, uint32_t nc) {
+  using E1 = typename std::conditional<kEs == 2, uint16_t, uint32_t>::type;
+  using E2 = typename std::conditional<kEs == 2, uint32_t, uint64_t>::type;
+  constexpr int32_t vw = 16 / kEs;
+  const Window x = row_window(w, nc, reinterpret_cast<uint64_t>(dst), kEs);
+  const int32_t m = x.hi > x.lo ? x.hi - x.lo : 0;
+  src += int64_t(x.lo) * kEs;
+  dst += int64_t(x.lo) * kEs;
+  // where the pieces lie: big ones towards the end of the window that is aligned
+  const uint32_t at = uint32_t(reinterpret_cast<uint64_t>(dst)) % 16u / kEs;
+  const bool inside = m < vw && at != 0 && at + uint32_t(m) != uint32_t(vw);  // the whole row, inside one unit
+  const int32_t e4 = at ? m & 3 : 0, e2 = at ? m & 1 : m & 4, e1 = at ? 0 : m & 6;
+  const bool p4 = kEs == 2 && !inside && (m & 4), p2 = !inside && (m & 2), p1 = !inside && (m & 1);
+  u32x4 v;  // each is stored only where it was loaded
+  uint64_t v4;
+  E2 v2;
+  E1 v1;
+  if (m == vw) v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(src));
+  if (m < vw) {
+    if (p4) __builtin_memcpy(&v4, src + e4 * kEs, 8);
+    if (p2) __builtin_memcpy(&v2, src + e2 * kEs, 2 * kEs);
+    if (p1) __builtin_memcpy(&v1, src + e1 * kEs, kEs);
+  }
+  // one wait for all of them: waits of their own would also wait for stores
+  __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt 0
+  if (m == vw) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst));
+  if (m < vw) {
+    if (p4) *reinterpret_cast<uint64_t*>(dst + e4 * kEs) = v4;
+    if (p2) *reinterpret_cast<E2*>(dst + e2 * kEs) = v2;
+    if (p1) *reinterpret_cast<E1*>(dst + e1 * kEs) = v1;
+    for (int32_t e = 0; inside && e < m; ++e) reinterpret_cast<E1*>(dst)[e] = reinterpret_cast<const E1*>(src)[e];
+  }
+}
+
 // ---------------------------------------------------------------------------
 // All four kinds: one sub-chunk of each kind per workgroup.
 
-// Sub-chunk j (kSub elements) of one kind of a tile.
-template <bool kPack, int kKind, uint32_t kSub>
-__device__ __forceinline__ void copy_sub_kind(const CopyArgs& a, const CopyBox& b, char* mbase,
-                                              const TileGeom& g, uint32_t j) {
-  using KT = KindTile<kPack, kKind>;
-  using E = typename KT::E;
-  constexpr int es = KT::es;
-  static_assert(kSub * es / 16 <= kSubThreads, "at most one vector per lane");
-  const KT k(a, b, mbase, g);
+// The tile's 16-byte vectors of sub-chunk j, one per lane at most.
+template <bool kPack, int kEs, uint32_t kSub>
+__device__ __forceinline__ void copy_sub_vectors(const KindTile<kPack, kEs>& k, const TileGeom& g, uint32_t j) {
+  constexpr uint32_t vw = 16 / kEs;
+  static_assert(kSub / vw <= kSubThreads, "at most one vector per lane");
+  const uint32_t vpr = g.nc / vw;
   uint32_t lo, hi;
-  if (sub_vectors(b, g, es)) {
-    constexpr uint32_t vw = 16 / es;
-    const uint32_t vpr = g.nc / vw;
-    sub_range(j, kSub / vw, g.nr * vpr, &lo, &hi);
-    const uint32_t i = lo + threadIdx.x;  // at most one vector per lane
-    if (i < hi) {
-      const uint32_t r = g.nr == 1 ? 0 : i / vpr;
-      const uint32_t c = i - r * vpr;
-      __builtin_nontemporal_store(
-          __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(k.src + r * k.sld + uint64_t(c) * 16)),
-          reinterpret_cast<u32x4*>(k.dst + r * k.dld + uint64_t(c) * 16));
-    }
-  } else {
-    sub_range(j, kSub, g.nr * g.nc, &lo, &hi);
-    const E* S = reinterpret_cast<const E*>(k.src);
-    E* D = reinterpret_cast<E*>(k.dst);
-    for (uint32_t i = lo + threadIdx.x; i < hi; i += kSubThreads) {
-      const uint32_t r = i / g.nc, c = i - r * g.nc;
-      D[r * (k.dld / es) + c] = S[r * (k.sld / es) + c];
-    }
+  sub_range(j, kSub / vw, g.nr * vpr, &lo, &hi);
+  const uint32_t i = lo + threadIdx.x;
+  if (i < hi) {
+    const uint32_t r = g.nr == 1 ? 0 : i / vpr;
+    const uint32_t c = i - r * vpr;
+    __builtin_nontemporal_store(
+        __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(k.src + r * k.sld + uint64_t(c) * 16)),
+        reinterpret_cast<u32x4*>(k.dst + r * k.dld + uint64_t(c) * 16));
   }
+}
+
+// Sub-chunk j (kSub elements) of one kind of a tile that moves in vectors.
+template <bool kPack, int kEs, uint32_t kSub>
+__device__ __forceinline__ void copy_sub(const CopyArgs& a, const CopyBox& b, char* mbase, const TileGeom& g,
+                                         uint32_t j, int kind) {
+  copy_sub_vectors<kPack, kEs, kSub>(KindTile<kPack, kEs>(a, b, mbase, g, kind), g, j);
+}
+
+// Sub-chunk j of one kind of a tile of any box, or, where the tile's rows do
+// not start on 128-byte lines, sub-chunk `run` in its place.
+template <bool kPack, int kEs, uint32_t kSub>
+__device__ __forceinline__ void copy_sub_any(const CopyArgs& a, const CopyBox& b, char* mbase, const TileGeom& g,
+                                             uint32_t j, uint32_t run, int kind) {
+  const KindTile<kPack, kEs> k(a, b, mbase, g, kind);
   if (kPack && j == 0 && g.last && b.pad) k.zero_pad(b);
+  const uint64_t bases = reinterpret_cast<uint64_t>(k.dst) | reinterpret_cast<uint64_t>(k.src);
+  if ((bases | (g.nr == 1 ? 0 : k.dld | k.sld)) % kLineBytes != 0) j = run;
+  if (sub_vectors(b, g, kEs)) {
+    copy_sub_vectors<kPack, kEs, kSub>(k, g, j);
+    return;
+  }
+  // windows j * kSub / vw ..., and past the nominal tile (rows of odd width
+  // touch more 16-byte units than they fill) the same windows of the next lap
+  constexpr uint32_t vw = 16 / kEs, per = kSub / vw, lap = kTileElems / vw;
+  const uint32_t wpr = windows_per_row(g.nc, kEs), n = g.nr * wpr;
+  if (threadIdx.x < per)
+    for (uint32_t i = j * per + threadIdx.x; i < n; i += lap) {
+      const uint32_t r = g.nr == 1 ? 0 : i / wpr;
+      copy_window<kEs>(k.src + r * k.sld, k.dst + r * k.dld, i - r * wpr, g.nc);
+    }
 }
 
 template <bool kPack>
 __global__ __launch_bounds__(kSubThreads) void copy_sub_kernel(CopyArgs a) {
-  const uint32_t t = blockIdx.x / kSubPerTile, j = blockIdx.x % kSubPerTile;
+  const uint32_t t = blockIdx.x / kSubPerTile;
+  uint32_t j = blockIdx.x % kSubPerTile;
   const uint32_t bi = box_of_tile(a.boxes, a.nbox, t);
   const CopyBox b = a.boxes[bi];
   const TileGeom g = tile_geom(b, t, a.boxes[bi + 1].tile0);
   char* mbase = a.peer[b.peer];
-  copy_sub_kind<kPack, 0, kSubElems>(a, b, mbase, g, j);
-  copy_sub_kind<kPack, 1, kSubElems>(a, b, mbase, g, j);
-  copy_sub_kind<kPack, 2, kSubElems>(a, b, mbase, g, j);
-  copy_sub_kind<kPack, 3, kSubElems>(a, b, mbase, g, j);
+  if (sub_vectors(b, g, 2) && sub_vectors(b, g, 4)) {
+    if (!(b.vec & kLineBox)) j = xcd_run(j, (g.nr * g.nc + kSubElems - 1) / kSubElems);
+    copy_sub<kPack, 2, kSubElems>(a, b, mbase, g, j, 0);
+    copy_sub<kPack, 4, kSubElems>(a, b, mbase, g, j, 1);
+    copy_sub<kPack, 4, kSubElems>(a, b, mbase, g, j, 2);
+    copy_sub<kPack, 4, kSubElems>(a, b, mbase, g, j, 3);
+    return;
+  }
+  const uint32_t used = sub_used(g);
+  if (j >= used) return;
+  const uint32_t run = xcd_run(j, used);
+  copy_sub_any<kPack, 2, kSubElems>(a, b, mbase, g, j, run, 0);
+#pragma unroll 1  // one body for the three kinds: code that a small launch has to fetch
+  for (int kind = 1; kind < 4; ++kind) copy_sub_any<kPack, 4, kSubElems>(a, b, mbase, g, j, run, kind);
 }
 
 // ---------------------------------------------------------------------------
 // One kind: kind_group(es) consecutive sub-chunks of kind_sub_elems(es)
 // elements of one tile per workgroup.
 
-template <bool kPack, int kKind>
-__device__ __forceinline__ void copy_kind_group(const CopyArgs& a) {
-  constexpr int es = kKind == 0 ? 2 : 4;
-  constexpr uint32_t sub = kind_sub_elems(es), grp = kind_group(es);
+template <bool kPack, int kEs>
+__global__ __launch_bounds__(kSubThreads) void copy_kind_kernel(CopyArgs a) {
+  constexpr uint32_t sub = kind_sub_elems(kEs), grp = kind_group(kEs);
   uint32_t t, q;
-  if (!kind_wg_tile(blockIdx.x, a.ntiles, es, &t, &q)) return;  // past the last tile
+  if (!kind_wg_tile(blockIdx.x, a.ntiles, kEs, &t, &q)) return;  // past the last tile
   const uint32_t bi = box_of_tile(a.boxes, a.nbox, t);
   const CopyBox b = a.boxes[bi];
   const TileGeom g = tile_geom(b, t, a.boxes[bi + 1].tile0);
   char* mbase = a.peer[b.peer];
+  if (sub_vectors(b, g, kEs)) {
+    // a 4-byte kind moves in vectors of 4 elements, and boxes end at multiples of 8
+    if (kPack && q == 0 && g.last && b.pad) KindTile<kPack, kEs>(a, b, mbase, g, a.kind).zero_pad(b);
 #pragma unroll
-  for (uint32_t i = 0; i < grp; ++i) copy_sub_kind<kPack, kKind, sub>(a, b, mbase, g, q * grp + i);
-}
-
-template <bool kPack>
-__global__ __launch_bounds__(kSubThreads) void copy_kind_kernel(CopyArgs a) {
-  switch (a.kind_mask) {
-    case 1: copy_kind_group<kPack, 0>(a); break;
-    case 2: copy_kind_group<kPack, 1>(a); break;
-    case 4: copy_kind_group<kPack, 2>(a); break;
-    case 8: copy_kind_group<kPack, 3>(a); break;
-    default: break;
+    for (uint32_t i = 0; i < grp; ++i) copy_sub<kPack, kEs, sub>(a, b, mbase, g, q * grp + i, a.kind);
+    return;
   }
+#pragma unroll 1
+  for (uint32_t i = 0; i < grp; ++i) copy_sub_any<kPack, kEs, sub>(a, b, mbase, g, q * grp + i, q * grp + i, a.kind);
 }
 
 // LDS reserved per workgroup of an all-kinds launch and never touched: with
@@ -176,19 +251,23 @@ hipError_t launch_copy(bool pack, const CopyBox* boxes, uint32_t nbox, uint32_t 
   a.boxes = boxes;
   a.nbox = nbox;
   a.ntiles = ntiles;
-  a.kind_mask = kind_mask;
+  a.kind = single ? __builtin_ctz(kind_mask) : 0;
   a.mode = mode;
   for (int k = 0; k < 4; ++k) a.arena[k] = static_cast<char*>(arena[k]);
   for (int p = 0; p < npeers; ++p) a.peer[p] = static_cast<char*>(peers[p]);
   const dim3 grid = dim3(uint32_t(nwg)), block = dim3(kSubThreads);
-  if (all && pack)
-    hipLaunchKernelGGL((copy_sub_kernel<true>), grid, block, kSubLdsBytes, stream, a);
-  else if (all)
-    hipLaunchKernelGGL((copy_sub_kernel<false>), grid, block, kSubLdsBytes, stream, a);
-  else if (pack)
-    hipLaunchKernelGGL((copy_kind_kernel<true>), grid, block, 0, stream, a);
-  else
-    hipLaunchKernelGGL((copy_kind_kernel<false>), grid, block, 0, stream, a);
+#define ETC_COPY(...) hipLaunchKernelGGL((__VA_ARGS__), grid, block, all ? kSubLdsBytes : 0, stream, a)
+  if (all) {
+    if (pack) ETC_COPY(copy_sub_kernel<true>);
+    else ETC_COPY(copy_sub_kernel<false>);
+  } else if (kind_mask == 1) {
+    if (pack) ETC_COPY(copy_kind_kernel<true, 2>);
+    else ETC_COPY(copy_kind_kernel<false, 2>);
+  } else {
+    if (pack) ETC_COPY(copy_kind_kernel<true, 4>);
+    else ETC_COPY(copy_kind_kernel<false, 4>);
+  }
+#undef ETC_COPY
   return hipGetLastError();
 }
 

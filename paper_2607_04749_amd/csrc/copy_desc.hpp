@@ -25,8 +25,12 @@ struct CopyBox {
   uint32_t tile0;     // first tile of this box in its launch
   uint16_t peer;      // peer slot
   uint8_t pad;        // zero elements after the box in the message (pack)
-  uint8_t vec;        // bit0: 16-byte vectors valid for 2-byte kinds, bit1: for 4-byte kinds
+  uint8_t vec;        // bit0: 16-byte vectors valid for 2-byte kinds, bit1: for 4-byte kinds; kLineBox
 };
+// CopyBox::vec bit: every row of the 4-byte kinds (six sevenths of the bytes)
+// starts on a 128-byte line on both sides.
+constexpr uint8_t kLineBox = 4;
+constexpr uint32_t kLineBytes = 128;
 static_assert(sizeof(CopyBox) == 64, "CopyBox layout");
 
 constexpr uint32_t kTileElems = 16384;  // nominal tile: 16384 elements per kind

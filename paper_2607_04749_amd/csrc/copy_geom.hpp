@@ -54,9 +54,9 @@ __host__ __device__ inline uint64_t tile_msg_elem(const CopyBox& b, const TileGe
 // kinds gives workgroup kSubPerTile * t + j sub-chunk j of tile t.  For each
 // kind, sub-chunk j covers the tile's vectors [j * kSubElems / vw,
 // (j + 1) * kSubElems / vw) when the kind moves in 16-byte vectors of vw
-// elements (one vector per lane at most), else its elements
-// [j * kSubElems, (j + 1) * kSubElems), both in row-major order over the
-// tile and clipped to the tile's size.
+// elements (one vector per lane at most), in row-major order over the tile and
+// clipped to its size; else the windows of as many vectors, and those a whole
+// tile of vectors further on.
 // A launch of one kind cuts a tile of that kind into kind_sub_elems(es)-element
 // sub-chunks instead and gives each workgroup kind_group(es) consecutive
 // ones of one tile.
@@ -111,7 +111,7 @@ __host__ __device__ inline bool kind_wg_tile(uint32_t w, uint32_t ntiles, int es
 
 // Whether the kind of element size es moves a tile in 16-byte vectors: the
 // box is vector-aligned for that size and every row of the tile is whole
-// vectors (a ragged single-row tile goes element by element).
+// vectors (other tiles move in windows, below).
 __host__ __device__ inline bool sub_vectors(const CopyBox& b, const TileGeom& g, int es) {
   return ((b.vec >> (es == 2 ? 0 : 1)) & 1) && g.nc % (16u / uint32_t(es)) == 0;
 }
@@ -121,6 +121,46 @@ __host__ __device__ inline void sub_range(uint32_t j, uint32_t per, uint32_t n, 
   const uint32_t a = j * per;
   *lo = a < n ? a : n;
   *hi = a + per < n ? a + per : n;
+}
+
+// Tiles that cannot move in aligned 16-byte vectors are cut into windows: the
+// 16-byte units of the target side that a row of the tile touches, in groups
+// of 64 bytes, so that no 64-byte sector is shared by two workgroups but at the
+// ends of a row.  A window that lies inside the row moves as one vector (its
+// load may be unaligned, its store is not), the first and last of a row in
+// smaller pieces.  Every row has windows_per_row of them, a few before its
+// start and past its end empty.  Groups of 16 and of 128 bytes measured up to
+// 3 % slower (rows of 1443 to 3813 elements) and 4 % slower (597 elements).
+constexpr uint32_t kSectorBytes = 64;
+__host__ __device__ inline uint32_t windows_per_row(uint32_t nc, int es) {
+  return (nc * uint32_t(es) + 2 * kSectorBytes - 1 - uint32_t(es)) / kSectorBytes * (kSectorBytes / 16u);
+}
+// Sub-chunks of an all-kinds launch past this many of a tile hold nothing of
+// any kind, in windows or (fewer) in vectors.
+__host__ __device__ inline uint32_t sub_used(const TileGeom& g) {
+  const uint32_t w4 = windows_per_row(g.nc, 4), w2 = 2 * windows_per_row(g.nc, 2);
+  const uint32_t n = (g.nr * (w4 > w2 ? w4 : w2) + kSubThreads - 1) / kSubThreads;
+  return n < kSubPerTile ? n : kSubPerTile;
+}
+// Elements [lo, hi) of a row of nc elements in its window w, where the row
+// starts at address `to` on the target side; empty when hi <= lo.
+struct Window {
+  int32_t lo, hi;
+};
+__host__ __device__ inline Window row_window(uint32_t w, uint32_t nc, uint64_t to, int es) {
+  const int32_t vw = 16 / es, at = int32_t(w) * vw - int32_t(uint32_t(to) & (kSectorBytes - 1)) / es;
+  return Window{at > 0 ? at : 0, at + vw < int32_t(nc) ? at + vw : int32_t(nc)};
+}
+
+// The hardware deals workgroup w to XCD w % kXcds.  Where a tile's rows do not
+// start on 128-byte lines, neighbouring sub-chunks share lines, and the L2 of
+// one XCD should see both: an order of the tile's sub-chunks in which each XCD
+// takes four consecutive ones out of every 4 * kXcds.  Sub-chunks past the
+// last 4 * kXcds that are all in use stay in place, or a tile of few
+// would keep some XCDs idle.
+__host__ __device__ inline uint32_t xcd_run(uint32_t j, uint32_t used) {
+  constexpr uint32_t m = 4 * kXcds - 1;
+  return (j | m) < used ? (j & ~m) | ((j & (kXcds - 1)) * 4) | ((j & m) / kXcds) : j;
 }
 
 // Byte offset of kind k's section inside a message of npad elements per section.

@@ -58,6 +58,11 @@ CopyBox make_box(uint64_t a_off, int64_t a_ld, int64_t rows, int64_t cols, uint6
     return true;
   };
   b.vec = uint8_t((ok(8) ? 1 : 0) | (ok(4) ? 2 : 0));
+  // a message's 4-byte kind sections start at multiples of 2 * npad bytes from a 256-byte boundary
+  constexpr uint64_t le = kLineBytes / 4;
+  if (a_off % le == 0 && m_off % le == 0 && msg_npad * 2 % kLineBytes == 0 &&
+      (rows == 1 || (uint64_t(a_ld) % le == 0 && uint64_t(m_ld) % le == 0)))
+    b.vec |= kLineBox;
   return b;
 }
 
