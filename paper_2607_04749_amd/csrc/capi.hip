@@ -69,21 +69,14 @@ hipError_t static_slot(int dev, StaticSlot** out) {
 
 void release_device(etc_plan_t* P) {
   if (P->device < 0) return;
-  if (P->static_gen) {  // tables in the static array: nothing to free
-    P->d_boxes = nullptr;
-    P->d_cost = nullptr;
-    P->d_home = nullptr;
-    P->d_failed = nullptr;
-    return;
+  if (P->d_block) {  // a static plan has no block of its own to free
+    int prev = -1;
+    const bool have_prev = hipGetDevice(&prev) == hipSuccess;
+    if (prev != P->device) (void)hipSetDevice(P->device);
+    (void)hipFree(P->d_block);
+    if (have_prev && prev != P->device) (void)hipSetDevice(prev);
   }
-  int prev = -1;
-  const bool have_prev = hipGetDevice(&prev) == hipSuccess;
-  if (prev != P->device) (void)hipSetDevice(P->device);
-  if (P->d_boxes) (void)hipFree(P->d_boxes);
-  if (P->d_cost) (void)hipFree(P->d_cost);
-  if (P->d_home) (void)hipFree(P->d_home);
-  if (P->d_failed) (void)hipFree(P->d_failed);
-  if (have_prev && prev != P->device) (void)hipSetDevice(prev);
+  P->d_block = nullptr;
   P->d_boxes = nullptr;
   P->d_cost = nullptr;
   P->d_home = nullptr;
@@ -191,77 +184,83 @@ int build_copy_tables(etc_plan_t* P, int rank, std::vector<etc::CopyBox>* all) {
   return ETC_OK;
 }
 
-// The cost kernel's table as it lies in device memory.
-void put_cost_table(const etc_plan_t& P, void* to) {
-  std::memcpy(to, P.cost.groups.data(), P.cost.first_byte());
-  std::memcpy(static_cast<char*>(to) + P.cost.first_byte(), P.cost.first.data(),
-              P.cost.first.size() * sizeof(uint32_t));
-}
+// A plan's device tables as one block: copy boxes, tensor groups, pairing,
+// failed ranks, each at a multiple of 256 bytes.
+struct DeviceTables {
+  std::vector<etc::CopyBox> boxes;
+  size_t o_cost = 0, o_home = 0, o_failed = 0, total = 0;
 
+  static size_t up(size_t n) { return (n + 255) / 256 * 256; }
+  // cost_bytes: room for the tensor groups
+  void place(const etc_plan_t& P, size_t cost_bytes) {
+    o_cost = up(boxes.size() * sizeof(etc::CopyBox));
+    o_home = o_cost + up(cost_bytes);
+    o_failed = o_home + up(P.home.size() * sizeof(int32_t));
+    total = o_failed + P.failed_bits.size() * sizeof(uint32_t);
+  }
+  std::vector<unsigned char> image(const etc_plan_t& P) const {
+    std::vector<unsigned char> img(std::max<size_t>(total, 1), 0);
+    std::memcpy(img.data(), boxes.data(), boxes.size() * sizeof(etc::CopyBox));
+    std::memcpy(img.data() + o_cost, P.cost.groups.data(), P.cost.first_byte());
+    std::memcpy(img.data() + o_cost + P.cost.first_byte(), P.cost.first.data(),
+                P.cost.first.size() * sizeof(uint32_t));
+    std::memcpy(img.data() + o_home, P.home.data(), P.home.size() * sizeof(int32_t));
+    std::memcpy(img.data() + o_failed, P.failed_bits.data(), P.failed_bits.size() * sizeof(uint32_t));
+    return img;
+  }
+  // point the plan at the block's tables
+  void bind(etc_plan_t* P, unsigned char* base) const {
+    P->d_boxes = boxes.empty() ? nullptr : reinterpret_cast<etc::CopyBox*>(base);
+    P->d_cost = reinterpret_cast<char*>(base + o_cost);
+    P->d_home = reinterpret_cast<int32_t*>(base + o_home);
+    P->d_failed = P->failed_bits.empty() ? nullptr : reinterpret_cast<uint32_t*>(base + o_failed);
+  }
+};
+
+// One allocation, one synchronous copy and one free for all of a plan's
+// tables rather than three or four of each: every such call goes through the
+// runtime's locks and waits for the device.
 int upload(etc_plan_t* P, int rank) {
-  using namespace etc;
   hipError_t e = hipGetDevice(&P->device);
   if (e != hipSuccess) {
     P->device = -1;
     return hip_fail(e, "hipGetDevice");
   }
-  std::vector<CopyBox> all;
-  int rc = build_copy_tables(P, rank, &all);
+  DeviceTables t;
+  int rc = build_copy_tables(P, rank, &t.boxes);
   if (rc) return rc;
-  if (!all.empty()) {
-    e = hipMalloc(&P->d_boxes, all.size() * sizeof(CopyBox));
-    if (e != hipSuccess) return fail(ETC_ERR_NOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
-    e = hipMemcpy(P->d_boxes, all.data(), all.size() * sizeof(CopyBox), hipMemcpyHostToDevice);
-    if (e != hipSuccess) return hip_fail(e, "hipMemcpy (copy tables)");
+  t.place(*P, P->cost.bytes());
+  const std::vector<unsigned char> img = t.image(*P);
+  e = hipMalloc(&P->d_block, img.size());
+  if (e != hipSuccess) {
+    P->d_block = nullptr;
+    return fail(ETC_ERR_NOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
   }
-  e = hipMalloc(&P->d_cost, P->cost.bytes());
-  if (e != hipSuccess) return fail(ETC_ERR_NOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
-  std::vector<char> cost(P->cost.bytes());
-  put_cost_table(*P, cost.data());
-  e = hipMemcpy(P->d_cost, cost.data(), cost.size(), hipMemcpyHostToDevice);
-  if (e != hipSuccess) return hip_fail(e, "hipMemcpy (tensor groups)");
-  e = hipMalloc(&P->d_home, std::max<size_t>(1, P->home.size()) * sizeof(int32_t));
-  if (e != hipSuccess) return fail(ETC_ERR_NOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
-  e = hipMemcpy(P->d_home, P->home.data(), P->home.size() * sizeof(int32_t), hipMemcpyHostToDevice);
-  if (e != hipSuccess) return hip_fail(e, "hipMemcpy (pairing)");
-  if (!P->failed_bits.empty()) {
-    e = hipMalloc(&P->d_failed, P->failed_bits.size() * sizeof(uint32_t));
-    if (e != hipSuccess) return fail(ETC_ERR_NOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
-    e = hipMemcpy(P->d_failed, P->failed_bits.data(), P->failed_bits.size() * sizeof(uint32_t),
-                  hipMemcpyHostToDevice);
-    if (e != hipSuccess) return hip_fail(e, "hipMemcpy (failed ranks)");
-  }
+  e = hipMemcpy(P->d_block, img.data(), img.size(), hipMemcpyHostToDevice);
+  if (e != hipSuccess) return hip_fail(e, "hipMemcpy (device tables)");
+  t.bind(P, static_cast<unsigned char*>(P->d_block));
   return ETC_OK;
 }
 
-// The same device tables written into the current device's static array:
-// copy boxes, tensor groups, pairing, failed ranks, each at a multiple of 256
-// bytes.  No device memory is allocated.
+// The same device tables written into the current device's static array.
+// No device memory is allocated.
 int upload_static(etc_plan_t* P, int rank) {
   using namespace etc;
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
-  std::vector<CopyBox> all;
-  int rc = build_copy_tables(P, rank, &all);
+  DeviceTables t;
+  int rc = build_copy_tables(P, rank, &t.boxes);
   if (rc) return rc;
-  auto up = [](size_t n) { return (n + 255) / 256 * 256; };
-  const size_t o_cg = up(all.size() * sizeof(CopyBox));
   // the tensor groups' room is counted as one RouteTensor per tensor, more
   // than they need: which plans fit the array does not depend on the grouping
-  const size_t o_home = o_cg + up(std::max(P->route_tensors.size() * sizeof(RouteTensor), P->cost.bytes()));
-  const size_t o_failed = o_home + up(P->home.size() * sizeof(int32_t));
-  const size_t total = o_failed + P->failed_bits.size() * sizeof(uint32_t);
-  if (total > size_t(ETC_STATIC_TABLE_BYTES))
-    return fail(ETC_ERR_UNSUPPORTED, "the plan's device tables need " + std::to_string(total) +
+  t.place(*P, std::max(P->route_tensors.size() * sizeof(RouteTensor), P->cost.bytes()));
+  if (t.total > size_t(ETC_STATIC_TABLE_BYTES))
+    return fail(ETC_ERR_UNSUPPORTED, "the plan's device tables need " + std::to_string(t.total) +
                                          " bytes; etc_plan_static holds at most " +
                                          std::to_string(int(ETC_STATIC_TABLE_BYTES)) +
                                          " (ETC_STATIC_TABLE_BYTES); use etc_plan, or a plan per process");
-  std::vector<unsigned char> img(std::max<size_t>(total, 1), 0);
-  std::memcpy(img.data(), all.data(), all.size() * sizeof(CopyBox));
-  put_cost_table(*P, img.data() + o_cg);
-  std::memcpy(img.data() + o_home, P->home.data(), P->home.size() * sizeof(int32_t));
-  std::memcpy(img.data() + o_failed, P->failed_bits.data(), P->failed_bits.size() * sizeof(uint32_t));
+  const std::vector<unsigned char> img = t.image(*P);
   std::unique_lock<std::shared_mutex> lock(g_static_mu);
   StaticSlot* slot = nullptr;
   if ((e = static_slot(dev, &slot)) != hipSuccess) return hip_fail(e, "hipGetSymbolAddress (static tables)");
@@ -270,13 +269,9 @@ int upload_static(etc_plan_t* P, int rank) {
   ++slot->gen;  // from here on, earlier static plans of this device are refused
   if ((e = hipMemcpy(slot->ptr, img.data(), img.size(), hipMemcpyHostToDevice)) != hipSuccess)
     return hip_fail(e, "hipMemcpy (static tables)");
-  unsigned char* base = static_cast<unsigned char*>(slot->ptr);
   P->device = dev;
   P->static_gen = slot->gen;
-  P->d_boxes = all.empty() ? nullptr : reinterpret_cast<CopyBox*>(base);
-  P->d_cost = reinterpret_cast<char*>(base + o_cg);
-  P->d_home = reinterpret_cast<int32_t*>(base + o_home);
-  P->d_failed = P->failed_bits.empty() ? nullptr : reinterpret_cast<uint32_t*>(base + o_failed);
+  t.bind(P, static_cast<unsigned char*>(slot->ptr));
   return ETC_OK;
 }
 

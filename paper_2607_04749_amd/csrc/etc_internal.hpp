@@ -177,6 +177,7 @@ struct etc_plan_s {
   // non-zero: the device tables live in the library's static array of that
   // device (etc_plan_static), written by its static_gen-th call there
   uint64_t static_gen = 0;
+  void* d_block = nullptr;  // the plan's own device allocation: all tables below (nullptr if static)
   char* d_cost = nullptr;  // device copy of cost: groups, then first
   int32_t* d_home = nullptr;  // device copy of home (D entries)
   uint32_t* d_failed = nullptr;  // device copy of failed_bits

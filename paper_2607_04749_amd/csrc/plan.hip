@@ -104,8 +104,8 @@ int stage_of(const LogicalTensor& t, int role, const Grid& g, int num_layers) {
   return -1;
 }
 
-RankLayout build_layout(const std::vector<LogicalTensor>& T, const Grid& g, int num_layers,
-                        int rank) {
+RankLayout build_layout(const std::vector<LogicalTensor>& T, const std::vector<RouteTensor>& stages, bool target,
+                        const Grid& g, int rank) {
   RankLayout L;
   const int pp = g.pp_of(rank), tp = g.tp_of(rank);  // every replica has the same layout
   const int nt = int(T.size());
@@ -115,8 +115,8 @@ RankLayout build_layout(const std::vector<LogicalTensor>& T, const Grid& g, int 
   int last_tensor = -1, last_role = -1;
   for (int role = 0; role < 2; ++role) {
     for (int i = 0; i < nt; ++i) {
+      if ((target ? stages[i].dst_stage : stages[i].src_stage)[role] != pp) continue;
       const LogicalTensor& t = T[i];
-      if (stage_of(t, role, g, num_layers) != pp) continue;
       Piece p{};
       p.tensor = i;
       p.role = role;
@@ -181,51 +181,80 @@ void check_model(const etc_model_desc& m) {
 }
 
 
-// Source ranks that may send part of tensor t to target d, ascending: a
-// superset of those for which routed_span is not empty.  They are the paired
-// source, and the ranks on the tensor's stages whose TP shard overlaps d's in
-// the replicas that may serve d: replica rep_d mod DP_src alone when no rank
-// failed (it always holds the tensor), every replica otherwise (failover).
-void candidate_senders(const RouteTensor& t, int d, int home, const RouteCtx& c,
-                       std::vector<int>* out) {
-  out->clear();
-  const int rd = d % (c.tpd * c.ppd);
-  const int tp_d = rd % c.tpd, rep_d = d / (c.tpd * c.ppd);
-  int tp_lo = 0, tp_hi = c.tps;  // source TP ranks [tp_lo, tp_hi)
-  if (t.split != kRepl) {
-    const Span need = shard_span(t, tp_d, c.tpd);
-    const int64_t w = split_extent(t) / c.tps;
-    tp_lo = int(need.lo / w);
-    tp_hi = int((need.hi + w - 1) / w);
+// A source rank that sends part of a tensor to a target: the LCM slices of
+// the split dim that it sends (the whole tensor, [0, 1), if replicated), and
+// the target's message from it (an index, -1 before its first box).
+struct Sender {
+  int s;
+  int64_t lo, hi;
+  int msg;
+};
+
+// The senders of target d, ascending, of the tensors whose copy roles lie on
+// the same source stages: the rules look at stages and TP ranks only, and two
+// shards of any split tensor overlap in the same LCM slices, so the layers of
+// a stage share one list (of a 70B model's 563 tensors a target has about six).
+struct SenderList {
+  int32_t src_stage[2] = {-2, -2};
+  int role_d = -1;
+  std::vector<Sender> senders;
+
+  bool is_for(const RouteTensor& t, int role) const {
+    return t.src_stage[0] == src_stage[0] && t.src_stage[1] == src_stage[1] && role == role_d;
   }
-  const int pt = c.tps * c.pps;
-  const int rep_lo = c.failed ? 0 : rep_d % c.dps, rep_hi = c.failed ? c.dps : rep_lo + 1;
-  for (int rep = rep_lo; rep < rep_hi; ++rep)
-    for (int r = 0; r < 2; ++r)
-      if (t.src_stage[r] >= 0)
-        for (int tp = tp_lo; tp < tp_hi; ++tp) out->push_back(rep * pt + t.src_stage[r] * c.tps + tp);
-  if (home >= 0) out->push_back(home);
-  std::sort(out->begin(), out->end());
-  out->erase(std::unique(out->begin(), out->end()), out->end());
-}
+  // Looks at the paired source, and the ranks on the tensors' stages whose TP
+  // shard overlaps d's in the replicas that may serve d: replica rep_d mod
+  // DP_src alone when no rank failed (it always holds the tensor), every
+  // replica otherwise (failover).
+  void build(const RouteTensor& t, int role, const TargetAt& b, const LcmSlices& lcm, const RouteCtx& c) {
+    src_stage[0] = t.src_stage[0];
+    src_stage[1] = t.src_stage[1];
+    role_d = role;
+    const bool repl = t.split == kRepl;
+    const Span need{repl ? 0 : b.tp * lcm.dst, repl ? 1 : (b.tp + 1) * lcm.dst};
+    const int tp_lo = repl ? 0 : int(need.lo / lcm.src), tp_hi = repl ? c.tps : int((need.hi - 1) / lcm.src) + 1;
+    const int pt = c.tps * c.pps;
+    const int rep_lo = c.failed ? 0 : b.rep0, rep_hi = c.failed ? c.dps : rep_lo + 1;
+    std::vector<int> cand;
+    for (int rep = rep_lo; rep < rep_hi; ++rep)
+      for (int r = 0; r < 2; ++r)
+        if (t.src_stage[r] >= 0)
+          for (int tp = tp_lo; tp < tp_hi; ++tp) cand.push_back(rep * pt + t.src_stage[r] * c.tps + tp);
+    if (b.home >= 0) cand.push_back(b.home);
+    std::sort(cand.begin(), cand.end());
+    cand.erase(std::unique(cand.begin(), cand.end()), cand.end());
+    senders.clear();
+    for (const int s : cand) {
+      const SourceAt a = source_at(s, c);
+      if (a.dead || role_on(t.src_stage, a.pp) < 0) continue;
+      const Span have{repl ? 0 : a.tp * lcm.src, repl ? 1 : (a.tp + 1) * lcm.src};
+      const Span x{std::max(have.lo, need.lo), std::min(have.hi, need.hi)};
+      if (x.len() != 0 && sends_shard(a, b, t.src_stage, repl, role, c)) senders.push_back(Sender{s, x.lo, x.hi, -1});
+    }
+  }
+};
 
 }  // namespace
 
 PlanError::PlanError(int c, std::string m) : std::runtime_error(std::move(m)), code(c) {}
 
+// Bound by one core's work on every rank's messages (of a plan that names one
+// process too: all ranks' layouts can be asked of it).  70B model, TP8xPP8xDP2 to
+// TP8xPP4xDP2 with a rank lost, on one core: 3.9 ms with the rules asked per
+// tensor and pair of ranks, 0.6 ms with sender lists; the whole etc_plan with its
+// sketch and device tables 2.25 ms and 0.38 ms on the machine of an MI355X.
 void build_host_plan(etc_plan_t& P) {
   const etc_model_desc& m = P.model;
-  P.tensors = build_tensor_table(m);
+  if (P.tensors.empty()) P.tensors = build_tensor_table(m);
   const int nt = int(P.tensors.size());
   const int S = P.src.world(), D = P.dst.world();
   if (int(P.home.size()) != D) fail(ETC_ERR_INVALID_ARG, "internal: pairing not set");
   const int Sr = P.src.replica_size(), Dr = P.dst.replica_size();
   P.src_layout.resize(Sr);
   P.dst_layout.resize(Dr);
-  for (int s = 0; s < Sr; ++s) P.src_layout[s] = build_layout(P.tensors, P.src, m.num_layers, s);
-  for (int d = 0; d < Dr; ++d) P.dst_layout[d] = build_layout(P.tensors, P.dst, m.num_layers, d);
-
   if (P.route_tensors.size() != size_t(nt)) build_route_tensors(P);
+  for (int s = 0; s < Sr; ++s) P.src_layout[s] = build_layout(P.tensors, P.route_tensors, false, P.src, s);
+  for (int d = 0; d < Dr; ++d) P.dst_layout[d] = build_layout(P.tensors, P.route_tensors, true, P.dst, d);
 
   const RouteCtx ctx = host_route_ctx(P);
   // Route every target piece: per target rank, per piece in arena order, the
@@ -234,17 +263,21 @@ void build_host_plan(etc_plan_t& P) {
   P.refer.assign(D, {});
   P.refer_elems.assign(D, 0);
   const bool direct_refer = (P.flags & ETC_PLAN_DIRECT_REFER) != 0;
-  std::vector<int> cand;
+  const LcmSlices lcm = lcm_slices(P);
+  const int64_t lcm_tp = lcm.src * P.src.tp;
   std::vector<etc_plan_s::Message> to_d;  // messages to the current target, by first box
   for (int d = 0; d < D; ++d) {
     to_d.clear();
+    const TargetAt at = target_at(d, P.home[d], ctx);
+    SenderList lists[2];  // of the last split and the last replicated tensor
     for (const Piece& q : P.dst_lay(d).pieces) {
       const RouteTensor& rt = P.route_tensors[q.tensor];
       uint64_t got = 0;
-      candidate_senders(rt, d, P.home[d], ctx, &cand);
-      for (const int s : cand) {
-        const Span x = routed_span(rt, s, d, P.home[d], ctx);
-        if (x.len() == 0) continue;
+      SenderList& from = lists[rt.split == kRepl];
+      if (!from.is_for(rt, q.role)) from.build(rt, q.role, at, lcm, ctx);
+      const int64_t unit = rt.split == kRepl ? 1 : split_extent(rt) / lcm_tp;
+      for (Sender& x : from.senders) {
+        const int s = x.s;
         etc_plan_s::MsgBox b{};
         b.tensor = q.tensor;
         b.role_d = q.role;
@@ -253,11 +286,11 @@ void build_host_plan(etc_plan_t& P) {
         b.c0 = 0;
         b.c1 = rt.cols;
         if (rt.split == kRows) {
-          b.r0 = x.lo;
-          b.r1 = x.hi;
+          b.r0 = x.lo * unit;
+          b.r1 = x.hi * unit;
         } else if (rt.split == kCols) {
-          b.c0 = x.lo;
-          b.c1 = x.hi;
+          b.c0 = x.lo * unit;
+          b.c1 = x.hi * unit;
         }
         const uint64_t n = uint64_t((b.r1 - b.r0) * (b.c1 - b.c0));
         got += n;
@@ -266,17 +299,20 @@ void build_host_plan(etc_plan_t& P) {
           P.refer_elems[d] += n;
           continue;
         }
-        auto it = std::find_if(to_d.begin(), to_d.end(), [&](const etc_plan_s::Message& x) { return x.s == s; });
-        if (it == to_d.end()) {
+        if (x.msg < 0)  // a message that an earlier list opened?
+          for (int i = 0; i < int(to_d.size()) && x.msg < 0; ++i)
+            if (to_d[size_t(i)].s == s) x.msg = i;
+        if (x.msg < 0) {
+          x.msg = int(to_d.size());
           to_d.emplace_back();
-          it = to_d.end() - 1;
-          it->s = s;
-          it->d = d;
+          to_d.back().s = s;
+          to_d.back().d = d;
         }
-        b.moff = it->npad;
-        it->npad += uint64_t(round_up(int64_t(n), 8));
-        it->elems += n;
-        it->boxes.push_back(b);
+        etc_plan_s::Message& to = to_d[size_t(x.msg)];
+        b.moff = to.npad;
+        to.npad += uint64_t(round_up(int64_t(n), 8));
+        to.elems += n;
+        to.boxes.push_back(b);
       }
       if (got != q.elems())
         fail(ETC_ERR_UNRECOVERABLE, "no live source rank holds part of " + P.tensors[q.tensor].name +
@@ -391,25 +427,24 @@ RouteCtx host_route_ctx(const etc_plan_t& P) {
 
 // COST of one data-parallel replica pair (Sec. III-B, bytes): rows are the
 // target ranks of a replica, columns the source ranks of one, COST[d][s] =
-// bytes(d) - OVERLAP[s][d] with the interval arithmetic of the cost kernel.
+// bytes(d) - OVERLAP[s][d] in the closed form of the cost kernel.
 // Every replica pair has this block, since a rank's workload depends only on
 // its TP and PP coordinates.
 std::vector<uint64_t> host_replica_cost(const etc_plan_t& P) {
   const int Sr = P.src.replica_size(), Dr = P.dst.replica_size();
+  const CostTable c = P.cost.first.empty() ? build_cost_table(P) : P.cost;
+  const LcmSlices lcm = lcm_slices(P);
   std::vector<uint64_t> cost(size_t(Dr) * Sr, 0);
   for (int d = 0; d < Dr; ++d) {
     const int pp_d = P.dst.pp_of(d), tp_d = P.dst.tp_of(d);
     for (int s = 0; s < Sr; ++s) {
       const int pp_s = P.src.pp_of(s), tp_s = P.src.tp_of(s);
+      const Span x{std::max(tp_s * lcm.src, tp_d * lcm.dst), std::min((tp_s + 1) * lcm.src, (tp_d + 1) * lcm.dst)};
       uint64_t need = 0, ov = 0;
-      for (const RouteTensor& t : P.route_tensors) {
-        if (role_on(t.dst_stage, pp_d) < 0) continue;
-        const Span want = shard_span(t, tp_d, P.dst.tp);
-        need += uint64_t(want.len() * unit_elems(t));
-        if (role_on(t.src_stage, pp_s) < 0) continue;
-        const Span have = shard_span(t, tp_s, P.src.tp);
-        const Span x{std::max(have.lo, want.lo), std::min(have.hi, want.hi)};
-        ov += uint64_t(x.len() * unit_elems(t));
+      for (uint32_t i = c.first[size_t(pp_d)]; i < c.first[size_t(pp_d) + 1]; ++i) {
+        const CostGroup& g = c.groups[i];
+        need += uint64_t(lcm.dst) * g.slice + g.whole;
+        if (role_on(g.src_stage, pp_s) >= 0) ov += uint64_t(x.len()) * g.slice + g.whole;
       }
       cost[size_t(d) * Sr + s] = (need - ov) * 14;
     }

@@ -16,7 +16,9 @@ struct PlanError : std::runtime_error {
 
 std::vector<LogicalTensor> build_tensor_table(const etc_model_desc& m);
 int stage_of(const LogicalTensor& t, int role, const Grid& g, int num_layers);
-RankLayout build_layout(const std::vector<LogicalTensor>& T, const Grid& g, int num_layers, int rank);
+// the layout of a rank of grid g, the plan's target grid or its source grid
+RankLayout build_layout(const std::vector<LogicalTensor>& T, const std::vector<RouteTensor>& stages, bool target,
+                        const Grid& g, int rank);
 
 // throws PlanError on bad input
 void validate(const etc_model_desc& m, const etc_parallel_cfg& src, const etc_parallel_cfg& dst);
