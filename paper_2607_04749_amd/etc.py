@@ -128,6 +128,7 @@ def _load():
 
 
 _lib = _load()
+_Pointers4 = ctypes.c_void_p * 4
 
 
 def lib():
@@ -148,7 +149,7 @@ def _ptr(x):
     return x.data_ptr()
 
 
-def _buf(x, need, what):
+def _buf(x, need, what, index=None):
     """Pointer of a device buffer that must hold at least `need` bytes.  A
     tensor must be a contiguous GPU tensor of that many bytes, else
     ValueError (the kernels would write past it); an integer pointer or None
@@ -156,19 +157,23 @@ def _buf(x, need, what):
     if x is None or isinstance(x, int):
         return x
     if not x.is_cuda or not x.is_contiguous():
-        raise ValueError(f"{what} must be a contiguous GPU tensor")
+        raise ValueError(f"{_item(what, index)} must be a contiguous GPU tensor")
     n = x.numel() * x.element_size()
     if n < need:
-        raise ValueError(f"{what} holds {n} bytes; the plan needs {need}")
+        raise ValueError(f"{_item(what, index)} holds {n} bytes; the plan needs {need}")
     return x.data_ptr()
+
+
+def _item(what, index):
+    return what if index is None else f"{what}[{index}]"
 
 
 def _arenas(plan, side, rank, arenas, what):
     """Pointers of a rank's four arenas, each checked as _buf does."""
     if len(arenas) != 4:
         raise ValueError(f"{what} needs 4 arenas, got {len(arenas)}")
-    e = plan.arena_elems(side, rank)
-    return [_buf(arenas[k], e * ESIZE[k], f"{what}[{k}]") for k in range(4)]
+    e = plan._arena_elems(side, rank)
+    return [_buf(arenas[k], e * ESIZE[k], what, k) for k in range(4)]
 
 
 def last_error():
@@ -195,6 +200,10 @@ class Plan:
         S, D = ctypes.c_int(), ctypes.c_int()
         _check(_lib.etc_plan_dims(handle, ctypes.byref(S), ctypes.byref(D)), "etc_plan_dims")
         self.S, self.D = S.value, D.value
+        # sizes that every device call checks its tensors against, by what
+        # they are of: a plan never changes, and asking the library anew took
+        # two thirds of a small call's time
+        self._sizes = {}
 
     @property
     def handle(self):
@@ -223,6 +232,32 @@ class Plan:
         _check(_lib.etc_plan_arena_elems(self.handle, side, rank, ctypes.byref(e)),
                "etc_plan_arena_elems")
         return e.value
+
+    def _size(self, key, ask):
+        if not self._h:
+            raise ValueError("plan was freed")
+        got = self._sizes.get(key)
+        if got is None:
+            got = self._sizes[key] = ask()
+        return got
+
+    def _arena_elems(self, side, rank):
+        return self._size((side, rank), lambda: self.arena_elems(side, rank))
+
+    def _out_layout(self, s, kind):
+        """(bytes of s's message to each target, length of its buffer): one
+        kind's chunk buffer, or the send buffer."""
+        _, per, _, total = self.send_layout(s) if kind is None else (None, *self.chunk_layout(s, kind))
+        return per, total
+
+    def _out_bytes(self, s, kind=None):
+        return self._size(("out", s, kind), lambda: self._out_layout(s, kind)[1])
+
+    def _msg_bytes(self, s, d, kind):
+        return self._size(("msg", s, d, kind), lambda: int(self._out_layout(s, kind)[0][d]))
+
+    def _home(self, d):
+        return self._size(("home", d), lambda: int(self.pairing()[d]))
 
     def arena_bytes(self, side, rank):
         e = self.arena_elems(side, rank)
@@ -373,10 +408,9 @@ def etc_pack(plan, src_rank, src_arenas, send_buf, stream=None):
     ok = _in_range(plan, SIDE_SRC, src_rank)
     a = _arenas(plan, SIDE_SRC, src_rank, src_arenas, "src_arenas") if ok else \
         [_ptr(x) for x in src_arenas]
-    need = plan.send_layout(src_rank)[3] if ok else 0
-    arr = (ctypes.c_void_p * 4)(*a)
-    _check(_lib.etc_pack(plan.handle, src_rank, ctypes.cast(arr, ctypes.c_void_p),
-                         _buf(send_buf, need, "send_buf"), _stream(stream)), "etc_pack")
+    need = plan._out_bytes(src_rank) if ok else 0
+    _check(_lib.etc_pack(plan.handle, src_rank, _Pointers4(*a), _buf(send_buf, need, "send_buf"),
+                         _stream(stream)), "etc_pack")
 
 
 def _msgs(plan, dst_rank, msgs, kind=None):
@@ -388,10 +422,8 @@ def _msgs(plan, dst_rank, msgs, kind=None):
     for s, x in enumerate(msgs):
         if x is None or isinstance(x, int) or not sized:
             out.append(_ptr(x))
-        elif kind is None:
-            out.append(_buf(x, int(plan.send_layout(s)[1][dst_rank]), f"msgs[{s}]"))
         else:
-            out.append(_buf(x, int(plan.chunk_layout(s, kind)[0][dst_rank]), f"msgs[{s}]"))
+            out.append(_buf(x, plan._msg_bytes(s, dst_rank, kind), "msgs", s))
     return (ctypes.c_void_p * plan.S)(*out)
 
 
@@ -401,15 +433,13 @@ def etc_unpack(plan, dst_rank, msgs, dst_arenas, stream=None):
     m = _msgs(plan, dst_rank, msgs)
     a = _arenas(plan, SIDE_DST, dst_rank, dst_arenas, "dst_arenas") \
         if _in_range(plan, SIDE_DST, dst_rank) else [_ptr(x) for x in dst_arenas]
-    arr = (ctypes.c_void_p * 4)(*a)
-    _check(_lib.etc_unpack(plan.handle, dst_rank, ctypes.cast(m, ctypes.c_void_p),
-                           ctypes.cast(arr, ctypes.c_void_p), _stream(stream)), "etc_unpack")
+    _check(_lib.etc_unpack(plan.handle, dst_rank, m, _Pointers4(*a), _stream(stream)), "etc_unpack")
 
 
 def _home(plan, dst_rank):
     if not _in_range(plan, SIDE_DST, dst_rank):
         return -1
-    return int(plan.pairing()[dst_rank])
+    return plan._home(dst_rank)
 
 
 def etc_refer(plan, dst_rank, src_arenas, dst_arenas, stream=None):
@@ -418,16 +448,14 @@ def etc_refer(plan, dst_rank, src_arenas, dst_arenas, stream=None):
     sa = _arenas(plan, SIDE_SRC, h, src_arenas, "src_arenas") if h >= 0 else [_ptr(x) for x in src_arenas]
     da = _arenas(plan, SIDE_DST, dst_rank, dst_arenas, "dst_arenas") if h >= 0 else \
         [_ptr(x) for x in dst_arenas]
-    src = (ctypes.c_void_p * 4)(*sa)
-    dst = (ctypes.c_void_p * 4)(*da)
-    _check(_lib.etc_refer(plan.handle, dst_rank, ctypes.cast(src, ctypes.c_void_p),
-                          ctypes.cast(dst, ctypes.c_void_p), _stream(stream)), "etc_refer")
+    _check(_lib.etc_refer(plan.handle, dst_rank, _Pointers4(*sa), _Pointers4(*da), _stream(stream)),
+           "etc_refer")
 
 
 def _kind_arena(plan, side, rank, kind, x, what):
     if not (0 <= kind < 4) or rank < 0 or not _in_range(plan, side, rank):
         return _ptr(x)
-    return _buf(x, plan.arena_elems(side, rank) * ESIZE[kind], what)
+    return _buf(x, plan._arena_elems(side, rank) * ESIZE[kind], what)
 
 
 def etc_refer_kind(plan, dst_rank, kind, src_arena, dst_arena, stream=None):
@@ -441,7 +469,7 @@ def etc_refer_kind(plan, dst_rank, kind, src_arena, dst_arena, stream=None):
 
 
 def etc_pack_kind(plan, src_rank, kind, src_arena, chunk_buf, stream=None):
-    need = plan.chunk_layout(src_rank, kind)[2] if _in_range(plan, SIDE_SRC, src_rank) and \
+    need = plan._out_bytes(src_rank, kind) if _in_range(plan, SIDE_SRC, src_rank) and \
         0 <= kind < 4 else 0
     _check(_lib.etc_pack_kind(plan.handle, src_rank, kind,
                               _kind_arena(plan, SIDE_SRC, src_rank, kind, src_arena, "src_arena"),
@@ -451,6 +479,6 @@ def etc_pack_kind(plan, src_rank, kind, src_arena, chunk_buf, stream=None):
 def etc_unpack_kind(plan, dst_rank, kind, msgs, dst_arena, stream=None):
     """msgs: S entries (tensor, int pointer or None), each in the chunk layout."""
     m = _msgs(plan, dst_rank, msgs, kind)
-    _check(_lib.etc_unpack_kind(plan.handle, dst_rank, kind, ctypes.cast(m, ctypes.c_void_p),
+    _check(_lib.etc_unpack_kind(plan.handle, dst_rank, kind, m,
                                 _kind_arena(plan, SIDE_DST, dst_rank, kind, dst_arena, "dst_arena"),
                                 _stream(stream)), "etc_unpack_kind")
