@@ -14,9 +14,13 @@
 // matrix: a thread stays in one column and the rows' coordinates are worked
 // out once per workgroup.  Llama-70B, MI355X, kernel time, against two
 // wavefronts per cell that looped over the 563 tensors:
-//   64 x 32 cells       COST 3.7 us, ROUTE 5.4 us    (6.6 to 8.5 us)
-//   1024 x 768 cells    COST 5.0 us, ROUTE 7.8 us, 11.5 us where a node of
+//   64 x 32 cells       COST 3.1-3.7 us, ROUTE 4.2-5.4 us    (6.6 to 8.5 us)
+//   1024 x 768 cells    COST 5.0 us, ROUTE 7.8 us, 11.2 us where a node of
 //                       8 ranks was lost             (1030 to 1360 us)
+// With ranks lost, a ROUTE cell loops only where its source's replica can stand
+// in (`reach`): COST + ROUTE took 13.7 us a pass, 14.1 while every replica's
+// cells looped.  The rest of those 11.2 us is one chain per cell: the groups one
+// after another, each with the holders' failed bits to read.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -68,14 +72,16 @@ __global__ __launch_bounds__(kCmThreads) void cost_kernel(const CostGroup* __res
   // the column's coordinates stay in registers, the rows' in LDS
   SourceAt a{};
   TargetAt b{};
-  bool lost = false;  // ROUTE: the replica that serves the target lost a rank
+  int reach = 0;  // ROUTE: the last replica, counted from the serving one, that may send to the target
   if (kCost) {
     a = source_at(mine, c);
     if (threadIdx.x < tile.rows && row0 + threadIdx.x < nrow)
       row_dst[threadIdx.x] = target_at(int(row0 + threadIdx.x), -1, c);
   } else {
     b = target_at(mine, kWhich == ETC_CM_ROUTE ? home[mine] : -1, c);
-    if (kWhich == ETC_CM_ROUTE) lost = any_dead(c, b.rep0 * c.tps * c.pps, c.tps * c.pps);
+    if (kWhich == ETC_CM_ROUTE)
+      for (int rep = b.rep0, n = c.tps * c.pps; reach + 1 < c.dps && any_dead(c, rep * n, n); ++reach)
+        rep = rep + 1 == c.dps ? 0 : rep + 1;
     if (threadIdx.x < tile.rows && row0 + threadIdx.x < nrow)
       row_src[threadIdx.x] = source_at(int(row0 + threadIdx.x), c);
   }
@@ -88,8 +94,9 @@ __global__ __launch_bounds__(kCmThreads) void cost_kernel(const CostGroup* __res
     bool held = !a.dead;  // whether the cell needs the loop over the groups
     if (kCost) held = held && a.rep == b.rep;
     if (kWhich == ETC_CM_OVERLAP_SHARDED) held = held && a.rep == b.rep0;
-    // a replica beyond the serving one stands in only where that one lost a rank
-    if (kWhich == ETC_CM_ROUTE) held = held && (a.rep == b.rep0 || a.s == b.home || lost);
+    // a replica beyond the serving one stands in only where that one and all between them lost ranks
+    if (kWhich == ETC_CM_ROUTE)
+      held = held && (a.s == b.home || (a.rep < b.rep0 ? a.rep - b.rep0 + c.dps : a.rep - b.rep0) <= reach);
     // elements of a slice / of whole tensors: moved or shared, and needed by the target
     uint64_t slice = 0, whole = 0, need_slice = 0, need_whole = 0;
     if (held) {

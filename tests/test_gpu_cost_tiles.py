@@ -24,6 +24,7 @@ UNTIED = ModelShape(LLAMA, 4, 24, 12, 12, 36, 24, 0, 0)
     (TIED, P(2, 2, 65), P(4, 1, 64), [0, 1, 4, 5, 259]),
     (UNTIED, P(4, 4, 16), P(4, 4, 33), [31, 32]),
     (UNTIED, P(1, 4, 64), P(2, 2, 64), list(range(8))),
+    (TIED, P(2, 1, 4), P(1, 2, 7), [6, 0, 1]),  # stand-ins past the last replica
 ])
 @pytest.mark.parametrize("placed", [False, True])
 def test_matrices_at_tile_edges(model, src, dst, failed, placed):
