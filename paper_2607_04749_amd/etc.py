@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+from operator import index
 
 import numpy as np
 # torch first: it loads its HIP runtime, and libetc.so (NEEDED libamdhip64.so.7)
@@ -149,7 +150,7 @@ def _ptr(x):
     return x.data_ptr()
 
 
-def _buf(x, need, what, index=None):
+def _buf(x, need, what, at=None):
     """Pointer of a device buffer that must hold at least `need` bytes.  A
     tensor must be a contiguous GPU tensor of that many bytes, else
     ValueError (the kernels would write past it); an integer pointer or None
@@ -157,15 +158,15 @@ def _buf(x, need, what, index=None):
     if x is None or isinstance(x, int):
         return x
     if not x.is_cuda or not x.is_contiguous():
-        raise ValueError(f"{_item(what, index)} must be a contiguous GPU tensor")
+        raise ValueError(f"{_item(what, at)} must be a contiguous GPU tensor")
     n = x.numel() * x.element_size()
     if n < need:
-        raise ValueError(f"{_item(what, index)} holds {n} bytes; the plan needs {need}")
+        raise ValueError(f"{_item(what, at)} holds {n} bytes; the plan needs {need}")
     return x.data_ptr()
 
 
-def _item(what, index):
-    return what if index is None else f"{what}[{index}]"
+def _item(what, at):
+    return what if at is None else f"{what}[{at}]"
 
 
 def _arenas(plan, side, rank, arenas, what):
@@ -202,7 +203,8 @@ class Plan:
         self.S, self.D = S.value, D.value
         # sizes that every device call checks its tensors against, by what
         # they are of: a plan never changes, and asking the library anew took
-        # two thirds of a small call's time
+        # two thirds of a small call's time.  Ranks and kinds in the keys are
+        # plain ints (a rank tensor hashes as the object, whatever it holds)
         self._sizes = {}
 
     @property
@@ -405,6 +407,7 @@ def _in_range(plan, side, rank):
 
 def etc_pack(plan, src_rank, src_arenas, send_buf, stream=None):
     """Tensors are checked against the plan's sizes (ValueError if short)."""
+    src_rank = index(src_rank)
     ok = _in_range(plan, SIDE_SRC, src_rank)
     a = _arenas(plan, SIDE_SRC, src_rank, src_arenas, "src_arenas") if ok else \
         [_ptr(x) for x in src_arenas]
@@ -430,6 +433,7 @@ def _msgs(plan, dst_rank, msgs, kind=None):
 def etc_unpack(plan, dst_rank, msgs, dst_arenas, stream=None):
     """msgs: S entries (tensor, int pointer or None).  Tensors are checked
     against the plan's sizes (ValueError if short)."""
+    dst_rank = index(dst_rank)
     m = _msgs(plan, dst_rank, msgs)
     a = _arenas(plan, SIDE_DST, dst_rank, dst_arenas, "dst_arenas") \
         if _in_range(plan, SIDE_DST, dst_rank) else [_ptr(x) for x in dst_arenas]
@@ -444,6 +448,7 @@ def _home(plan, dst_rank):
 
 def etc_refer(plan, dst_rank, src_arenas, dst_arenas, stream=None):
     """Refer: dst_rank's kept data from its paired source's arenas into its own."""
+    dst_rank = index(dst_rank)
     h = _home(plan, dst_rank)
     sa = _arenas(plan, SIDE_SRC, h, src_arenas, "src_arenas") if h >= 0 else [_ptr(x) for x in src_arenas]
     da = _arenas(plan, SIDE_DST, dst_rank, dst_arenas, "dst_arenas") if h >= 0 else \
@@ -460,6 +465,7 @@ def _kind_arena(plan, side, rank, kind, x, what):
 
 def etc_refer_kind(plan, dst_rank, kind, src_arena, dst_arena, stream=None):
     """etc_refer for one state kind (that kind's arenas)."""
+    dst_rank, kind = index(dst_rank), index(kind)
     h = _home(plan, dst_rank)
     _check(_lib.etc_refer_kind(plan.handle, dst_rank, kind,
                                _kind_arena(plan, SIDE_SRC, h, kind, src_arena, "src_arena"),
@@ -469,6 +475,7 @@ def etc_refer_kind(plan, dst_rank, kind, src_arena, dst_arena, stream=None):
 
 
 def etc_pack_kind(plan, src_rank, kind, src_arena, chunk_buf, stream=None):
+    src_rank, kind = index(src_rank), index(kind)
     need = plan._out_bytes(src_rank, kind) if _in_range(plan, SIDE_SRC, src_rank) and \
         0 <= kind < 4 else 0
     _check(_lib.etc_pack_kind(plan.handle, src_rank, kind,
@@ -478,6 +485,7 @@ def etc_pack_kind(plan, src_rank, kind, src_arena, chunk_buf, stream=None):
 
 def etc_unpack_kind(plan, dst_rank, kind, msgs, dst_arena, stream=None):
     """msgs: S entries (tensor, int pointer or None), each in the chunk layout."""
+    dst_rank, kind = index(dst_rank), index(kind)
     m = _msgs(plan, dst_rank, msgs, kind)
     _check(_lib.etc_unpack_kind(plan.handle, dst_rank, kind, m,
                                 _kind_arena(plan, SIDE_DST, dst_rank, kind, dst_arena, "dst_arena"),
