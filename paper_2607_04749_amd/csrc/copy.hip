@@ -168,9 +168,8 @@ __device__ __forceinline__ void copy_sub_any(const CopyArgs& a, const CopyBox& b
     copy_sub_vectors<kPack, kEs, kSub>(k, g, j);
     return;
   }
-  // windows j * kSub / vw ..., and past the nominal tile (rows of odd width
-  // touch more 16-byte units than they fill) the same windows of the next lap
-  constexpr uint32_t vw = 16 / kEs, per = kSub / vw, lap = kTileElems / vw;
+  // windows [j * per, (j + 1) * per), and in a one-row tile the same windows of the next lap
+  constexpr uint32_t per = kSub / (16 / kEs), lap = lap_windows(kEs);
   const uint32_t wpr = windows_per_row(g.nc, kEs), n = g.nr * wpr;
   if (threadIdx.x < per)
     for (uint32_t i = j * per + threadIdx.x; i < n; i += lap) {

@@ -135,6 +135,10 @@ constexpr uint32_t kSectorBytes = 64;
 __host__ __device__ inline uint32_t windows_per_row(uint32_t nc, int es) {
   return (nc * uint32_t(es) + 2 * kSectorBytes - 1 - uint32_t(es)) / kSectorBytes * (kSectorBytes / 16u);
 }
+// Windows in one pass of a tile's sub-chunks.  Tiles of several rows hold no
+// more (tiles.hip); a one-row tile may, and the first sub-chunks then take
+// the rest in a second pass.
+__host__ __device__ constexpr uint32_t lap_windows(int es) { return kTileElems / (16u / uint32_t(es)); }
 // Sub-chunks of an all-kinds launch past this many of a tile hold nothing of
 // any kind, in windows or (fewer) in vectors.
 __host__ __device__ inline uint32_t sub_used(const TileGeom& g) {

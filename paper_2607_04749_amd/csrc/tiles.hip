@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <string>
 
+#include "copy_geom.hpp"
 #include "etc_internal.hpp"
 #include "plan.hpp"
 #include "route.hpp"
@@ -23,6 +24,11 @@ void fail(int code, const std::string& msg) { throw PlanError(code, msg); }
 // carry over to the pieces.
 constexpr int64_t kMaxRunElems = int64_t(1) << 31;
 
+// Rows of a tile of whole rows: as many as kTileElems elements hold.
+uint32_t rows_by_elems(int64_t rows, int64_t cols) {
+  return uint32_t(std::max<int64_t>(1, std::min<int64_t>(rows, kTileElems / cols)));
+}
+
 // Fill the copy descriptor of one box with its tiles starting at tile0.
 // m_ld: row stride on the message side (cols for a message, whose boxes are
 // row-major; a source arena's row stride for a Refer box).
@@ -38,18 +44,6 @@ CopyBox make_box(uint64_t a_off, int64_t a_ld, int64_t rows, int64_t cols, uint6
   b.a_ld = uint32_t(a_ld);
   b.rows = uint32_t(rows);
   b.cols = uint32_t(cols);
-  if (cols >= int64_t(kTileElems)) {
-    b.tc = kTileElems;
-    b.tr = 1;
-  } else {
-    b.tc = uint32_t(cols);
-    b.tr = uint32_t(std::max<int64_t>(1, std::min<int64_t>(rows, kTileElems / cols)));
-  }
-  b.ntc = uint32_t((cols + b.tc - 1) / b.tc);
-  b.tile0 = tile0;
-  b.peer = uint16_t(peer);
-  const uint64_t n = uint64_t(rows) * uint64_t(cols);
-  b.pad = pack ? uint8_t((8 - n % 8) % 8) : 0;
   // 16-byte vectors: 8 elements of a 2-byte kind, 4 of a 4-byte kind.  The
   // message side starts every box at a multiple of 8 elements.
   auto ok = [&](uint64_t w) {
@@ -57,6 +51,26 @@ CopyBox make_box(uint64_t a_off, int64_t a_ld, int64_t rows, int64_t cols, uint6
     if (rows > 1 && (uint64_t(a_ld) % w || uint64_t(cols) % w || uint64_t(m_ld) % w)) return false;
     return true;
   };
+  if (cols >= int64_t(kTileElems)) {
+    b.tc = kTileElems;
+    b.tr = 1;
+  } else {
+    b.tc = uint32_t(cols);
+    // Rows that move in windows touch more 16-byte units than they fill: as
+    // many rows as one pass of the tile's sub-chunks takes, of either size.
+    // Tiles of kTileElems elements left a second pass to the first few
+    // workgroups of each: rows of 454 and 681 elements 70.1 -> 65.4 us (a
+    // 6-layer model's migration), 597 elements 855 -> 812 us, one kind at a
+    // time up to 150 -> 100 us (rows of 27 to 113).
+    b.tr = rows_by_elems(rows, cols);
+    for (int es : {2, 4})
+      if (!ok(16 / es)) b.tr = std::max(1u, std::min(b.tr, lap_windows(es) / windows_per_row(b.tc, es)));
+  }
+  b.ntc = uint32_t((cols + b.tc - 1) / b.tc);
+  b.tile0 = tile0;
+  b.peer = uint16_t(peer);
+  const uint64_t n = uint64_t(rows) * uint64_t(cols);
+  b.pad = pack ? uint8_t((8 - n % 8) % 8) : 0;
   b.vec = uint8_t((ok(8) ? 1 : 0) | (ok(4) ? 2 : 0));
   // a message's 4-byte kind sections start at multiples of 2 * npad bytes from a 256-byte boundary
   constexpr uint64_t le = kLineBytes / 4;
@@ -99,6 +113,23 @@ void add_box(std::vector<CopyBox>& v, uint32_t& tiles, uint64_t a_off, int64_t a
   push(make_box(a_off, a_ld, rows, cols, m_off, msg_npad, peer, pack, tiles, m_ld));
 }
 
+// End a launch table with its sentinel.  A launch past the grid limit is first
+// cut into tiles by elements, the fewest there can be, so that which ranks
+// are refused does not depend on the width of their rows.
+void finish(std::vector<CopyBox>& v, uint32_t tiles) {
+  if (uint64_t(tiles) * kSubPerTile > uint64_t(INT32_MAX)) {
+    tiles = 0;
+    for (CopyBox& b : v) {
+      if (b.tc == b.cols) b.tr = rows_by_elems(b.rows, b.cols);
+      b.tile0 = tiles;
+      tiles += box_tiles(b);
+    }
+  }
+  CopyBox sentinel{};
+  sentinel.tile0 = tiles;
+  v.push_back(sentinel);
+}
+
 }  // namespace
 
 std::vector<CopyBox> build_pack_boxes(const etc_plan_t& P, int s, std::vector<int32_t>* peers,
@@ -122,9 +153,7 @@ std::vector<CopyBox> build_pack_boxes(const etc_plan_t& P, int s, std::vector<in
       moved += uint64_t((b.r1 - b.r0) * (b.c1 - b.c0)) * 14;
     }
   }
-  CopyBox sentinel{};
-  sentinel.tile0 = tiles;
-  v.push_back(sentinel);
+  finish(v, tiles);
   if (bytes) *bytes = moved;
   return v;
 }
@@ -149,9 +178,7 @@ std::vector<CopyBox> build_unpack_boxes(const etc_plan_t& P, int d, std::vector<
       moved += uint64_t((b.r1 - b.r0) * (b.c1 - b.c0)) * 14;
     }
   }
-  CopyBox sentinel{};
-  sentinel.tile0 = tiles;
-  v.push_back(sentinel);
+  finish(v, tiles);
   if (bytes) *bytes = moved;
   return v;
 }
@@ -174,9 +201,7 @@ std::vector<CopyBox> build_refer_boxes(const etc_plan_t& P, int d, uint64_t* byt
       moved += uint64_t((b.r1 - b.r0) * (b.c1 - b.c0)) * 14;
     }
   }
-  CopyBox sentinel{};
-  sentinel.tile0 = tiles;
-  v.push_back(sentinel);
+  finish(v, tiles);
   if (bytes) *bytes = moved;
   return v;
 }

@@ -111,6 +111,8 @@ static void replay_sub(const std::vector<CopyBox>& v, bool pack, bool sectioned,
       const uint32_t unit = vk ? 16u / uint32_t(es) : 1u;  // elements per item
       const uint32_t per = sub_elems / unit;               // items per sub-chunk
       const uint32_t ipr = g.nc / unit;                    // items per row
+      if (!vk && g.nr > 1 && g.nr * windows_per_row(g.nc, es) > kTileElems / (16u / uint32_t(es)))
+        FAIL("a tile of %u rows of %u elements has windows for a second pass", g.nr, g.nc);
       if (vk && per > kSubThreads) FAIL("a vector sub-chunk needs more lanes than threads");
       if (!all && es != kes) FAIL("one-kind launch of another element size");
       if (vk && g.nc % unit) FAIL("vector rows not whole vectors");
