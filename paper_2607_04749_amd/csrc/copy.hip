@@ -87,11 +87,11 @@ struct KindTile {
   }
 };
 
-// Window w of a row of nc elements.  The first and last window of a row move
-// as up to three pieces of 4, 2 and 1 elements, each aligned on the target
-// side.  All of a wavefront's loads are issued before any store: most
-// wavefronts hold an end of some row, and a second load after the first
-// store would double their time.
+// Window w of a row of nc elements, as one vector or up to three pieces.  All
+// of a wavefront's loads are issued before any store: most wavefronts hold an
+// end of some row, and a second load after the first store would double their
+// time.  (Rows inside one 16-byte unit went element by element, a load and a
+// store in turn: tiny boxes of 5-wide rows 3 to 5 % slower than in pieces.)
 template <int kEs>
 __device__ __forceinline__ void copy_window(const char* src, char* dst, uint32_t w, uint32_t nc) {
   using E1 = typename std::conditional<kEs == 2, uint16_t, uint32_t>::type;
@@ -101,29 +101,24 @@ __device__ __forceinline__ void copy_window(const char* src, char* dst, uint32_t
   const int32_t m = x.hi > x.lo ? x.hi - x.lo : 0;
   src += int64_t(x.lo) * kEs;
   dst += int64_t(x.lo) * kEs;
-  // where the pieces lie: big ones towards the end of the window that is aligned
-  const uint32_t at = uint32_t(reinterpret_cast<uint64_t>(dst)) % 16u / kEs;
-  const bool inside = m < vw && at != 0 && at + uint32_t(m) != uint32_t(vw);  // the whole row, inside one unit
-  const int32_t e4 = at ? m & 3 : 0, e2 = at ? m & 1 : m & 4, e1 = at ? 0 : m & 6;
-  const bool p4 = kEs == 2 && !inside && (m & 4), p2 = !inside && (m & 2), p1 = !inside && (m & 1);
+  const Pieces p = window_pieces(m, uint32_t(reinterpret_cast<uint64_t>(dst)) % 16u / kEs, kEs);
   u32x4 v;  // each is stored only where it was loaded
   uint64_t v4;
   E2 v2;
   E1 v1;
   if (m == vw) v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(src));
   if (m < vw) {
-    if (p4) __builtin_memcpy(&v4, src + e4 * kEs, 8);
-    if (p2) __builtin_memcpy(&v2, src + e2 * kEs, 2 * kEs);
-    if (p1) __builtin_memcpy(&v1, src + e1 * kEs, kEs);
+    if (kEs == 2 && p.p4) __builtin_memcpy(&v4, src + p.e4 * kEs, 8);
+    if (p.p2) __builtin_memcpy(&v2, src + p.e2 * kEs, 2 * kEs);
+    if (p.p1) __builtin_memcpy(&v1, src + p.e1 * kEs, kEs);
   }
   // one wait for all of them: waits of their own would also wait for stores
   __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt 0
   if (m == vw) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst));
   if (m < vw) {
-    if (p4) *reinterpret_cast<uint64_t*>(dst + e4 * kEs) = v4;
-    if (p2) *reinterpret_cast<E2*>(dst + e2 * kEs) = v2;
-    if (p1) *reinterpret_cast<E1*>(dst + e1 * kEs) = v1;
-    for (int32_t e = 0; inside && e < m; ++e) reinterpret_cast<E1*>(dst)[e] = reinterpret_cast<const E1*>(src)[e];
+    if (kEs == 2 && p.p4) __builtin_memcpy(dst + p.e4 * kEs, &v4, 8);
+    if (p.p2) __builtin_memcpy(dst + p.e2 * kEs, &v2, 2 * kEs);
+    if (p.p1) __builtin_memcpy(dst + p.e1 * kEs, &v1, kEs);
   }
 }
 

@@ -131,9 +131,17 @@ __host__ __device__ inline void sub_range(uint32_t j, uint32_t per, uint32_t n, 
 // smaller pieces.  Every row has windows_per_row of them, a few before its
 // start and past its end empty.  Groups of 16 and of 128 bytes measured up to
 // 3 % slower (rows of 1443 to 3813 elements) and 4 % slower (597 elements).
-constexpr uint32_t kSectorBytes = 64;
+// Rows of less than 512 bytes go without the grouping: most of their windows
+// would be empty (a row of 3 elements has 2 windows, or 8 in a group).  Packs
+// and unpacks with rows of 7 to 113 elements took 1 to 15 % less time that
+// way, 1 to 4 % less than with the line at 128 bytes and as much as at 256.
+constexpr uint32_t kSectorBytes = 64, kNarrowBytes = 512;
+__host__ __device__ inline uint32_t window_group(uint32_t nc, int es) {
+  return nc * uint32_t(es) < kNarrowBytes ? 16u : kSectorBytes;
+}
 __host__ __device__ inline uint32_t windows_per_row(uint32_t nc, int es) {
-  return (nc * uint32_t(es) + 2 * kSectorBytes - 1 - uint32_t(es)) / kSectorBytes * (kSectorBytes / 16u);
+  const uint32_t g = window_group(nc, es);
+  return (nc * uint32_t(es) + 2 * g - 1 - uint32_t(es)) / g * (g / 16u);
 }
 // Windows in one pass of a tile's sub-chunks.  Tiles of several rows hold no
 // more (tiles.hip); a one-row tile may, and the first sub-chunks then take
@@ -152,8 +160,24 @@ struct Window {
   int32_t lo, hi;
 };
 __host__ __device__ inline Window row_window(uint32_t w, uint32_t nc, uint64_t to, int es) {
-  const int32_t vw = 16 / es, at = int32_t(w) * vw - int32_t(uint32_t(to) & (kSectorBytes - 1)) / es;
+  const int32_t vw = 16 / es, at = int32_t(w) * vw - int32_t(uint32_t(to) & (window_group(nc, es) - 1)) / es;
   return Window{at > 0 ? at : 0, at + vw < int32_t(nc) ? at + vw : int32_t(nc)};
+}
+
+// The pieces of 4, 2 and 1 elements that a window of m < 16 / es elements moves
+// in (p: whether there is one, e: its first element), where the window starts
+// `at` elements into its 16-byte unit of the target side.  The last window of
+// a row starts its unit and the first one ends it: big pieces lie towards that
+// end, so each is aligned on the target side.  Those of a row inside one unit
+// need not be.
+struct Pieces {
+  bool p4, p2, p1;
+  int32_t e4, e2, e1;
+};
+__host__ __device__ inline Pieces window_pieces(int32_t m, uint32_t at, int es) {
+  const bool first = at != 0 && at + uint32_t(m) == 16u / uint32_t(es);
+  return Pieces{es == 2 && (m & 4) != 0, (m & 2) != 0, (m & 1) != 0,
+                first ? m & 3 : 0, first ? m & 1 : m & 4, first ? 0 : m & 6};
 }
 
 // The hardware deals workgroup w to XCD w % kXcds.  Where a tile's rows do not

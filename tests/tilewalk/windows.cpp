@@ -1,6 +1,7 @@
 // windows.cpp -- host replay of the copy kernels' window walk (copy_geom.hpp):
-// rows of every length and start, each element in exactly one window, a full
-// window on a 16-byte boundary of the target.  Test code.
+// rows of every length and start, each element in exactly one window or piece
+// of one, a full window on a 16-byte boundary of the target; a row of few
+// elements in no more windows than elements.  Test code.
 #include <cstdio>
 #include <vector>
 #include "copy_geom.hpp"
@@ -9,6 +10,7 @@ using namespace etc;
 static int check(uint32_t nc, int es, uint64_t to) {
   const int vw = 16 / es;
   std::vector<int> hits(nc, 0);
+  if (nc > 1 && windows_per_row(nc, es) > nc) return 7;
   for (uint32_t w = 0; w < windows_per_row(nc, es); ++w) {
     const Window x = row_window(w, nc, to, es);
     if (x.hi <= x.lo) continue;
@@ -16,7 +18,20 @@ static int check(uint32_t nc, int es, uint64_t to) {
     if (x.hi - x.lo == vw && (to + uint64_t(x.lo) * es) % 16) return 2;
     // a smaller window touches one 16-byte unit only
     if ((to + uint64_t(x.lo) * es) / 16 != (to + uint64_t(x.hi) * es - 1) / 16) return 3;
-    for (int32_t e = x.lo; e < x.hi; ++e) ++hits[size_t(e)];
+    if (x.hi - x.lo == vw) {
+      for (int32_t e = x.lo; e < x.hi; ++e) ++hits[size_t(e)];
+      continue;
+    }
+    const uint64_t at = to + uint64_t(x.lo) * es;
+    const Pieces p = window_pieces(x.hi - x.lo, uint32_t(at % 16) / es, es);
+    const bool inside = at % 16 && (at + uint64_t(x.hi - x.lo) * es) % 16;
+    const struct { bool is; int32_t e, n; } pieces[3] = {{p.p4, p.e4, 4}, {p.p2, p.e2, 2}, {p.p1, p.e1, 1}};
+    for (const auto& q : pieces) {
+      if (!q.is) continue;
+      if (x.lo + q.e < 0 || x.lo + q.e + q.n > int32_t(nc)) return 5;
+      if (!inside && (at + uint64_t(q.e) * es) % (uint64_t(q.n) * es)) return 6;  // a store off its boundary
+      for (int32_t e = q.e; e < q.e + q.n; ++e) ++hits[size_t(x.lo + e)];
+    }
   }
   for (uint32_t e = 0; e < nc; ++e)
     if (hits[e] != 1) return 4;
