@@ -153,9 +153,8 @@ __device__ __forceinline__ void copy_sub(const CopyArgs& a, const CopyBox& b, ch
 // Sub-chunk j of one kind of a tile of any box, or, where the tile's rows do
 // not start on 128-byte lines, sub-chunk `run` in its place.
 template <bool kPack, int kEs, uint32_t kSub>
-__device__ __forceinline__ void copy_sub_any(const CopyArgs& a, const CopyBox& b, char* mbase, const TileGeom& g,
-                                             uint32_t j, uint32_t run, int kind) {
-  const KindTile<kPack, kEs> k(a, b, mbase, g, kind);
+__device__ __forceinline__ void copy_sub_any(const KindTile<kPack, kEs>& k, const CopyBox& b, const TileGeom& g,
+                                             uint32_t j, uint32_t run) {
   if (kPack && j == 0 && g.last && b.pad) k.zero_pad(b);
   const uint64_t bases = reinterpret_cast<uint64_t>(k.dst) | reinterpret_cast<uint64_t>(k.src);
   if ((bases | (g.nr == 1 ? 0 : k.dld | k.sld)) % kLineBytes != 0) j = run;
@@ -192,9 +191,10 @@ __global__ __launch_bounds__(kSubThreads) void copy_sub_kernel(CopyArgs a) {
   const uint32_t used = sub_used(g);
   if (j >= used) return;
   const uint32_t run = xcd_run(j, used);
-  copy_sub_any<kPack, 2, kSubElems>(a, b, mbase, g, j, run, 0);
+  copy_sub_any<kPack, 2, kSubElems>(KindTile<kPack, 2>(a, b, mbase, g, 0), b, g, j, run);
 #pragma unroll 1  // one body for the three kinds: code that a small launch has to fetch
-  for (int kind = 1; kind < 4; ++kind) copy_sub_any<kPack, 4, kSubElems>(a, b, mbase, g, j, run, kind);
+  for (int kind = 1; kind < 4; ++kind)
+    copy_sub_any<kPack, 4, kSubElems>(KindTile<kPack, 4>(a, b, mbase, g, kind), b, g, j, run);
 }
 
 // ---------------------------------------------------------------------------
@@ -209,16 +209,18 @@ __global__ __launch_bounds__(kSubThreads) void copy_kind_kernel(CopyArgs a) {
   const uint32_t bi = box_of_tile(a.boxes, a.nbox, t);
   const CopyBox b = a.boxes[bi];
   const TileGeom g = tile_geom(b, t, a.boxes[bi + 1].tile0);
-  char* mbase = a.peer[b.peer];
+  // once per workgroup: with the kind known at launch only, the compiler would
+  // work it out anew for every sub-chunk (tiny boxes 7 to 11 % slower)
+  const KindTile<kPack, kEs> k(a, b, a.peer[b.peer], g, a.kind);
   if (sub_vectors(b, g, kEs)) {
     // a 4-byte kind moves in vectors of 4 elements, and boxes end at multiples of 8
-    if (kPack && q == 0 && g.last && b.pad) KindTile<kPack, kEs>(a, b, mbase, g, a.kind).zero_pad(b);
+    if (kPack && q == 0 && g.last && b.pad) k.zero_pad(b);
 #pragma unroll
-    for (uint32_t i = 0; i < grp; ++i) copy_sub<kPack, kEs, sub>(a, b, mbase, g, q * grp + i, a.kind);
+    for (uint32_t i = 0; i < grp; ++i) copy_sub_vectors<kPack, kEs, sub>(k, g, q * grp + i);
     return;
   }
 #pragma unroll 1
-  for (uint32_t i = 0; i < grp; ++i) copy_sub_any<kPack, kEs, sub>(a, b, mbase, g, q * grp + i, q * grp + i, a.kind);
+  for (uint32_t i = 0; i < grp; ++i) copy_sub_any<kPack, kEs, sub>(k, b, g, q * grp + i, q * grp + i);
 }
 
 // LDS reserved per workgroup of an all-kinds launch and never touched: with
