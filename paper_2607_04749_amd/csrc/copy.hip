@@ -18,8 +18,8 @@
 // Either way a workgroup finds its tile's descriptor once (a binary search of
 // the tile table, scalar loads) and then moves a few KB.  The hardware
 // dispatches the workgroups in index order, so the whole GPU advances
-// through each buffer as one compact front; an all-kinds launch reserves
-// LDS so that at most 25 of its workgroups share a CU (kSubLdsBytes).  On MI355X this ran 5-14 %
+// through each buffer as one compact front; all-kinds and large one-kind launches reserve
+// LDS so that at most 25 of their workgroups share a CU (kSubLdsBytes).  On MI355X this ran 5-14 %
 // faster than a persistent grid of one deep-batched workgroup per CU for all
 // four kinds, and up to 9 % faster for one kind, and it holds its rate where
 // the persistent grid lost about 10 % to an unfavourable relative placement
@@ -223,15 +223,21 @@ __global__ __launch_bounds__(kSubThreads) void copy_kind_kernel(CopyArgs a) {
   for (uint32_t i = 0; i < grp; ++i) copy_sub_any<kPack, kEs, sub>(k, b, g, q * grp + i, q * grp + i);
 }
 
-// LDS reserved per workgroup of an all-kinds launch and never touched: with
+// LDS reserved per workgroup and never touched, in all-kinds launches: with
 // 160 KB of LDS per CU it lets at most 25 of these one-wave workgroups share
 // a CU, where they would otherwise fill its 32 wave slots.  The copy keeps
 // HBM's queues full either way.  With fewer requests queued, MI355X ran the
 // 70B and 7B shares 2-3 % faster in their slower buffer placements, and
 // every other all-kinds launch measured within -1 to +1.6 %.  A cap of 21
-// workgroups ran 1-3.5 % below the cap of 25.  One-kind launches, whose
-// workgroups move 8 KB each, lost with any cap and keep all 32 slots.
+// workgroups ran 1-3.5 % below the cap of 25.  A one-kind launch, whose
+// workgroups spend less of their time on finding their tile, runs 0.3 to 3 %
+// faster with the cap from four rounds of all wave slots on (13B, 70B and 7B
+// steps one kind at a time: 11637 -> 11312, 15227 -> 14777 and 11807 -> 11506
+// us).  Smaller ones, where the rounds are few, ran from 3 % faster to 6 %
+// slower (6400 to 8192 workgroups: two rounds instead of one) and keep all 32
+// slots of a CU.
 constexpr unsigned kSubLdsBytes = 6400;
+constexpr uint64_t kCappedKindGrid = 4 * 256 * 32;
 
 }  // namespace
 
@@ -252,7 +258,8 @@ hipError_t launch_copy(bool pack, const CopyBox* boxes, uint32_t nbox, uint32_t 
   for (int k = 0; k < 4; ++k) a.arena[k] = static_cast<char*>(arena[k]);
   for (int p = 0; p < npeers; ++p) a.peer[p] = static_cast<char*>(peers[p]);
   const dim3 grid = dim3(uint32_t(nwg)), block = dim3(kSubThreads);
-#define ETC_COPY(...) hipLaunchKernelGGL((__VA_ARGS__), grid, block, all ? kSubLdsBytes : 0, stream, a)
+  const unsigned lds = all || nwg >= kCappedKindGrid ? kSubLdsBytes : 0;
+#define ETC_COPY(...) hipLaunchKernelGGL((__VA_ARGS__), grid, block, lds, stream, a)
   if (all) {
     if (pack) ETC_COPY(copy_sub_kernel<true>);
     else ETC_COPY(copy_sub_kernel<false>);
