@@ -201,9 +201,10 @@ struct DeviceTables {
   std::vector<unsigned char> image(const etc_plan_t& P) const {
     std::vector<unsigned char> img(std::max<size_t>(total, 1), 0);
     std::memcpy(img.data(), boxes.data(), boxes.size() * sizeof(etc::CopyBox));
-    std::memcpy(img.data() + o_cost, P.cost.groups.data(), P.cost.first_byte());
-    std::memcpy(img.data() + o_cost + P.cost.first_byte(), P.cost.first.data(),
-                P.cost.first.size() * sizeof(uint32_t));
+    const etc::CostTable& c = P.cost;
+    std::memcpy(img.data() + o_cost, c.stages.data(), c.stages.size() * sizeof(etc::CostStage));
+    std::memcpy(img.data() + o_cost + c.pairs_byte(), c.pairs.data(), c.pairs.size() * sizeof(etc::CostPair));
+    std::memcpy(img.data() + o_cost + c.groups_byte(), c.groups.data(), c.groups.size() * sizeof(etc::CostGroup));
     std::memcpy(img.data() + o_home, P.home.data(), P.home.size() * sizeof(int32_t));
     std::memcpy(img.data() + o_failed, P.failed_bits.data(), P.failed_bits.size() * sizeof(uint32_t));
     return img;
@@ -601,9 +602,8 @@ int etc_cost_matrix(const etc_plan_t* P, int which, uint64_t* d_out, void* strea
     return fail(ETC_ERR_UNSUPPORTED, "a cost matrix is limited to 2^31 - 1 cells");
   const etc::RouteCtx ctx{P->src.tp, P->src.pp, P->src.dp, P->dst.tp, P->dst.pp, P->dst.dp,
                          P->d_failed};
-  hipError_t e = etc::launch_cost(reinterpret_cast<const etc::CostGroup*>(P->d_cost),
-                                  reinterpret_cast<const uint32_t*>(P->d_cost + P->cost.first_byte()), P->d_home,
-                                  ctx, etc::lcm_slices(*P), which, d_out, static_cast<hipStream_t>(stream));
+  hipError_t e = etc::launch_cost(P->cost.view(P->d_cost), P->d_home, ctx, etc::lcm_slices(*P), which, d_out,
+                                  static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "cost matrix launch");
   return ETC_OK;
 }

@@ -55,7 +55,7 @@ struct RankLayout {
 };
 
 // ---------------------------------------------------------------------------
-// Per-tensor routing record, shared by the host planner and the cost kernel
+// Per-tensor routing record of the host planner
 // ---------------------------------------------------------------------------
 
 struct RouteTensor {
@@ -66,27 +66,60 @@ struct RouteTensor {
   int32_t single_copy;   // exactly one copy in both grids
 };
 
-// What the cost kernel reads in place of the tensors: all tensors that a
-// target stage holds in copy role role_d and whose roles lie on the same source
-// stages, summed.  A split dim divides by both TP degrees, hence by their
-// least common multiple, so a pair of shards of any split tensor overlaps in
-// the same number of LCM slices (Sec. III-C) and the tensors' slices add up;
-// replicated tensors count whole.
+// What the cost kernel reads in place of the tensors: their sizes summed by
+// target stage and source stages.  A split dim divides by both TP degrees,
+// hence by their least common multiple, so a pair of shards of any split
+// tensor overlaps in the same number of LCM slices (Sec. III-C) and the
+// tensors' slices add up; replicated tensors count whole.  Sizes are elements:
+// `slice`, of one LCM slice of the split tensors, and `whole`, of the replicated.
+
+// The tensors that a target stage holds in copy role role_d and whose roles
+// lie on the same source stages.
 struct CostGroup {
   int32_t src_stage[2];  // as in RouteTensor
-  int32_t role_d, stage_d;
-  uint64_t slice, whole;    // elements: one LCM slice of the split tensors; the replicated ones
-  uint64_t slice1, whole1;  // the same over single-copy tensors
+  int32_t role_d, unused;
+  uint64_t slice, whole;
 };
-static_assert(sizeof(CostGroup) == 48, "CostGroup layout");
+static_assert(sizeof(CostGroup) == 32, "CostGroup layout");
 
-// The groups by target stage, and for every target stage the index of its
-// first group (one more entry ends the last stage's).
+// The tensors that a target stage and a source stage both hold: their groups
+// [first, end), and the groups' sums.
+struct CostPair {
+  uint64_t slice, whole;
+  uint64_t slice1, whole1;  // the same over single-copy tensors
+  uint32_t first, end;
+};
+static_assert(sizeof(CostPair) == 40, "CostPair layout");
+
+// A target stage: the sums over all its tensors, and its pairs with source
+// stages lo, lo + 1, ..., n of them, from pair `first` on.  The other source
+// stages hold none of its tensors.
+struct CostStage {
+  uint64_t slice, whole;
+  int32_t lo;
+  uint32_t n, first, unused;
+};
+static_assert(sizeof(CostStage) == 32, "CostStage layout");
+
+// The three tables, as arrays.  A cell reads its target's stage, one pair, and for ROUTE that pair's groups.
+struct CostView {
+  const CostStage* stages;
+  const CostPair* pairs;
+  const CostGroup* groups;
+};
+
 struct CostTable {
-  std::vector<CostGroup> groups;
-  std::vector<uint32_t> first;
-  size_t first_byte() const { return groups.size() * sizeof(CostGroup); }  // the groups, then `first`
-  size_t bytes() const { return first_byte() + first.size() * sizeof(uint32_t); }
+  std::vector<CostStage> stages;  // one per target stage
+  std::vector<CostPair> pairs;
+  std::vector<CostGroup> groups;  // one on two source stages is in two pairs' lists
+  // device memory: the stages, the pairs, the groups
+  size_t pairs_byte() const { return stages.size() * sizeof(CostStage); }
+  size_t groups_byte() const { return pairs_byte() + pairs.size() * sizeof(CostPair); }
+  size_t bytes() const { return groups_byte() + groups.size() * sizeof(CostGroup); }
+  CostView view(const char* base) const {
+    return CostView{reinterpret_cast<const CostStage*>(base), reinterpret_cast<const CostPair*>(base + pairs_byte()),
+                    reinterpret_cast<const CostGroup*>(base + groups_byte())};
+  }
 };
 
 // Launch table of one rank's pack or unpack.
@@ -111,8 +144,8 @@ struct LcmSlices {
   int64_t src, dst;
 };
 
-hipError_t launch_cost(const CostGroup* groups, const uint32_t* first, const int32_t* home, RouteCtx ctx,
-                       LcmSlices lcm, int which, uint64_t* out, hipStream_t stream);
+hipError_t launch_cost(const CostView& tables, const int32_t* home, RouteCtx ctx, LcmSlices lcm, int which,
+                       uint64_t* out, hipStream_t stream);
 
 }  // namespace etc
 
@@ -178,7 +211,7 @@ struct etc_plan_s {
   // device (etc_plan_static), written by its static_gen-th call there
   uint64_t static_gen = 0;
   void* d_block = nullptr;  // the plan's own device allocation: all tables below (nullptr if static)
-  char* d_cost = nullptr;  // device copy of cost: groups, then first
+  char* d_cost = nullptr;  // device copy of cost, laid out as its view() has it
   int32_t* d_home = nullptr;  // device copy of home (D entries)
   uint32_t* d_failed = nullptr;  // device copy of failed_bits
   etc::CopyBox* d_boxes = nullptr;

@@ -396,27 +396,54 @@ LcmSlices lcm_slices(const etc_plan_t& P) {
 
 CostTable build_cost_table(const etc_plan_t& P) {
   const int64_t lcm = std::lcm(int64_t(P.src.tp), int64_t(P.dst.tp));
+  struct Sums {
+    uint64_t slice = 0, whole = 0, slice1 = 0, whole1 = 0;
+  };
   // by target stage, then target role and source stages
-  std::map<std::array<int32_t, 4>, CostGroup> sums;
+  std::map<std::array<int32_t, 4>, Sums> sums;
   for (const RouteTensor& t : P.route_tensors)
     for (int role = 0; role < 2; ++role) {
       if (t.dst_stage[role] < 0) continue;
-      CostGroup& g = sums[{t.dst_stage[role], role, t.src_stage[0], t.src_stage[1]}];
+      Sums& g = sums[{t.dst_stage[role], role, t.src_stage[0], t.src_stage[1]}];
       const uint64_t n = t.split == kRepl ? uint64_t(unit_elems(t)) : uint64_t(split_extent(t) / lcm * unit_elems(t));
       (t.split == kRepl ? g.whole : g.slice) += n;
       if (t.single_copy) (t.split == kRepl ? g.whole1 : g.slice1) += n;
     }
   CostTable c;
-  c.first.assign(size_t(P.dst.pp) + 1, 0);
-  for (auto& [key, g] : sums) {
-    g.stage_d = key[0];
-    g.role_d = key[1];
-    g.src_stage[0] = key[2];
-    g.src_stage[1] = key[3];
-    c.groups.push_back(g);
-    ++c.first[size_t(g.stage_d) + 1];
+  c.stages.reserve(size_t(P.dst.pp));
+  c.groups.reserve(2 * sums.size());
+  c.pairs.reserve(size_t(P.dst.pp) + 3 * size_t(P.src.pp));
+  auto g = sums.begin();
+  for (int pp = 0; pp < P.dst.pp; ++pp) {
+    const auto from = g;
+    CostStage st{0, 0, P.src.pp, 0, uint32_t(c.pairs.size()), 0};
+    int hi = -1;
+    for (; g != sums.end() && g->first[0] == pp; ++g) {
+      st.slice += g->second.slice;
+      st.whole += g->second.whole;
+      for (int i = 2; i < 4; ++i)
+        if (g->first[i] >= 0) {
+          st.lo = std::min(st.lo, g->first[i]);
+          hi = std::max(hi, int(g->first[i]));
+        }
+    }
+    for (int s = st.lo; s <= hi; ++s, ++st.n) {
+      CostPair p{0, 0, 0, 0, uint32_t(c.groups.size()), 0};
+      for (auto k = from; k != g; ++k) {
+        const auto& [key, x] = *k;
+        const int32_t stages[2] = {key[2], key[3]};
+        if (role_on(stages, s) < 0) continue;
+        p.slice += x.slice;
+        p.whole += x.whole;
+        p.slice1 += x.slice1;
+        p.whole1 += x.whole1;
+        c.groups.push_back(CostGroup{{key[2], key[3]}, key[1], 0, x.slice, x.whole});
+      }
+      p.end = uint32_t(c.groups.size());
+      c.pairs.push_back(p);
+    }
+    c.stages.push_back(st);
   }
-  for (size_t i = 1; i < c.first.size(); ++i) c.first[i] += c.first[i - 1];
   return c;
 }
 
@@ -432,19 +459,22 @@ RouteCtx host_route_ctx(const etc_plan_t& P) {
 // its TP and PP coordinates.
 std::vector<uint64_t> host_replica_cost(const etc_plan_t& P) {
   const int Sr = P.src.replica_size(), Dr = P.dst.replica_size();
-  const CostTable c = P.cost.first.empty() ? build_cost_table(P) : P.cost;
+  const CostTable built = P.cost.stages.empty() ? build_cost_table(P) : CostTable{};
+  const CostTable& c = P.cost.stages.empty() ? built : P.cost;
   const LcmSlices lcm = lcm_slices(P);
   std::vector<uint64_t> cost(size_t(Dr) * Sr, 0);
   for (int d = 0; d < Dr; ++d) {
-    const int pp_d = P.dst.pp_of(d), tp_d = P.dst.tp_of(d);
+    const int tp_d = P.dst.tp_of(d);
+    const CostStage& st = c.stages[size_t(P.dst.pp_of(d))];
+    const uint64_t need = uint64_t(lcm.dst) * st.slice + st.whole;
     for (int s = 0; s < Sr; ++s) {
       const int pp_s = P.src.pp_of(s), tp_s = P.src.tp_of(s);
       const Span x{std::max(tp_s * lcm.src, tp_d * lcm.dst), std::min((tp_s + 1) * lcm.src, (tp_d + 1) * lcm.dst)};
-      uint64_t need = 0, ov = 0;
-      for (uint32_t i = c.first[size_t(pp_d)]; i < c.first[size_t(pp_d) + 1]; ++i) {
-        const CostGroup& g = c.groups[i];
-        need += uint64_t(lcm.dst) * g.slice + g.whole;
-        if (role_on(g.src_stage, pp_s) >= 0) ov += uint64_t(x.len()) * g.slice + g.whole;
+      uint64_t ov = 0;
+      const uint32_t at = uint32_t(pp_s - st.lo);
+      if (at < st.n) {
+        const CostPair& p = c.pairs[st.first + at];
+        ov = uint64_t(x.len()) * p.slice + p.whole;
       }
       cost[size_t(d) * Sr + s] = (need - ov) * 14;
     }

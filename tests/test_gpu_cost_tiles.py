@@ -13,6 +13,8 @@ pytestmark = pytest.mark.gpu
 
 TIED = ModelShape(GPT, 4, 24, 12, 12, 36, 24, 8, 1)
 UNTIED = ModelShape(LLAMA, 4, 24, 12, 12, 36, 24, 0, 0)
+TIED16 = ModelShape(GPT, 16, 24, 12, 12, 36, 24, 8, 1)
+UNTIED16 = ModelShape(LLAMA, 16, 24, 12, 12, 36, 24, 0, 0)
 
 
 @pytest.mark.parametrize("model,src,dst,failed", [
@@ -25,6 +27,10 @@ UNTIED = ModelShape(LLAMA, 4, 24, 12, 12, 36, 24, 0, 0)
     (UNTIED, P(4, 4, 16), P(4, 4, 33), [31, 32]),
     (UNTIED, P(1, 4, 64), P(2, 2, 64), list(range(8))),
     (TIED, P(2, 1, 4), P(1, 2, 7), [6, 0, 1]),  # stand-ins past the last replica
+    (TIED16, P(1, 16, 1), P(1, 1, 1), []),  # many source stages of one target stage
+    (TIED16, P(2, 1, 2), P(1, 16, 3), [1]),
+    (UNTIED16, P(2, 16, 3), P(4, 2, 2), [5, 40]),
+    (UNTIED16, P(4, 8, 1), P(3, 16, 1), []),
 ])
 @pytest.mark.parametrize("placed", [False, True])
 def test_matrices_at_tile_edges(model, src, dst, failed, placed):

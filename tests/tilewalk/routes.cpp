@@ -71,6 +71,34 @@ int main() {
         }
         expect(cost[size_t(d) * Sr + s] == (need - ov) * 14, "COST differs from the sum over the tensors", it);
       }
+    // the cost kernel's tables: a pair lists each of its groups once and no
+    // other, and they fit the room that static plans count for them
+    const CostTable table = build_cost_table(P);
+    expect(table.bytes() <= P.route_tensors.size() * sizeof(RouteTensor), "the cost tables need more room", it);
+    for (int pd = 0; pd < P.dst.pp; ++pd)
+      for (int ps = 0; ps < P.src.pp; ++ps) {
+        const CostStage& st = table.stages[pd];
+        const uint32_t at = uint32_t(ps - st.lo);
+        const CostPair p = at < st.n ? table.pairs[st.first + at] : CostPair{};
+        uint64_t held = 0, held1 = 0, listed = 0;  // elements per LCM slice, or of a whole tensor
+        for (const RouteTensor& t : P.route_tensors) {
+          if (role_on(t.dst_stage, pd) < 0 || role_on(t.src_stage, ps) < 0) continue;
+          const uint64_t n = uint64_t(unit_elems(t)) *
+                             (t.split == kRepl ? 1 : split_extent(t) / (lcm_slices(P).src * P.src.tp));
+          held += n;
+          held1 += t.single_copy ? n : 0;
+        }
+        for (uint32_t i = p.first; i < p.end; ++i) {
+          const CostGroup& g = table.groups[i];
+          listed += g.slice + g.whole;
+          expect(role_on(g.src_stage, ps) >= 0, "a group of another source stage", it);
+          for (uint32_t k = p.first; k < i; ++k)
+            expect(g.role_d != table.groups[k].role_d || g.src_stage[0] != table.groups[k].src_stage[0] ||
+                       g.src_stage[1] != table.groups[k].src_stage[1], "a group listed twice", it);
+        }
+        expect(p.end - p.first <= 3 && listed == held, "a pair's groups are not its tensors", it);
+        expect(p.slice + p.whole == held && p.slice1 + p.whole1 == held1, "a pair's sums are not its tensors", it);
+      }
     {  // the same matrix 2^k times over: past 2^59 the sketch works in 128 bits
       std::vector<uint64_t> big = cost;
       const uint64_t top = *std::max_element(cost.begin(), cost.end());
