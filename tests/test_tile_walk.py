@@ -1,7 +1,8 @@
 """The copy tables on the host, no GPU: tests/tilewalk/tilewalk.cpp replays the
-copy kernels' sub-chunk walk over every launch the planner builds (pack,
-unpack, Refer; all kinds and one kind at a time) and checks bounds,
-alignment and exact write coverage.  Plans: the five
+copy kernels' sub-chunk walk (vectors, or windows and their pieces, in the order
+of the XCD runs) over every launch the planner builds (pack, unpack, Refer;
+all kinds and one kind at a time) and checks bounds, alignment and exact write
+coverage.  Plans: the five
 workloads, micro models, data parallelism with failed ranks, coalesced and
 random configurations, under the identity pairing, the sketch and direct
 Refer.  This is the check run on the CPU before a plan shape first runs on
@@ -16,7 +17,7 @@ import pytest
 
 import oracle
 from micro import MICRO_MODELS, cfg_pairs
-from paper_2607_04749_amd.workloads import WORKLOADS, Parallel as P
+from paper_2607_04749_amd.workloads import GPT, LLAMA, WORKLOADS, ModelShape, Parallel as P
 from randcfg import cases, medium_cases
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -178,3 +179,53 @@ def test_replay_catches_a_planted_geometry_mistake(tmp_path, plant):
     for args in (_args(w.model, w.src, w.dst, False, "identity"), _args(w.model, w.src, w.dst, True, "sketch")):
         r = subprocess.run([exe, *args], capture_output=True, text=True, timeout=600)
         assert r.returncode != 0 and r.stdout.strip() != "ok", (plant, " ".join(args))
+
+
+# a Llama whose shards are odd numbers of elements wide (681 to 454, 84 to 252)
+RAGGED = ModelShape(LLAMA, 4, 504, 12, 6, 1362, 5004, 0, 0)
+WINDOW_PLANTS = {
+    # the last windows of a row are missing: its end is never copied
+    "a row short of windows": ("/ g * (g / 16u);", "/ g * (g / 16u) - 1;"),
+    # workgroups that still hold windows return at once
+    "used sub-chunks rounded down": ("+ kSubThreads - 1) / kSubThreads;", "- 1) / kSubThreads;"),
+    # the two-element piece of a row's last window one element on
+    "a piece out of place": ("first ? m & 1 : m & 4", "first ? m & 1 : (m & 4) + (m & 1)"),
+    # runs of two in the layout of runs of four: sub-chunks copied twice, others never
+    "a run order that is no permutation": ("((j & m) / kXcds)", "((j & m) / kXcds / 2)"),
+    # windows counted from the wrong unit of the target
+    "windows off their units": ("to) & (window_group(nc, es) - 1)", "to) & (window_group(nc, es) / 2 - 1)"),
+}
+
+
+@pytest.mark.parametrize("plant", sorted(WINDOW_PLANTS))
+def test_replay_catches_a_planted_window_mistake(tmp_path, plant):
+    """As above, in what only tiles of odd widths use."""
+    old, new = WINDOW_PLANTS[plant]
+    src = open(os.path.join(CSRC, "copy_geom.hpp")).read()
+    assert src.count(old) == 1
+    (tmp_path / "copy_geom.hpp").write_text(src.replace(old, new))
+    exe = str(tmp_path / "tilewalk")
+    # the planner's sources too take the copy: a quoted include looks beside its file first
+    for f in os.listdir(CSRC):
+        if f != "copy_geom.hpp":
+            (tmp_path / f).write_text(open(os.path.join(CSRC, f)).read())
+    subprocess.run(["hipcc", "-x", "hip", "-O2", "-std=c++17", "--offload-arch=gfx950",
+                    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                    "-I", str(tmp_path), "-I", os.path.join(ROOT, "include"), SRC,
+                    *[str(tmp_path / x) for x in LIB_SOURCES], "-o", exe],
+                   check=True, capture_output=True)
+    for args in (_args(RAGGED, P(3, 1), P(2, 1), False, "identity"), _args(RAGGED, P(3, 1), P(2, 1), True, "sketch")):
+        r = subprocess.run([exe, *args], capture_output=True, text=True, timeout=600)
+        assert r.returncode != 0 and r.stdout.strip() != "ok", (plant, " ".join(args))
+
+
+def test_odd_widths(tilewalk):
+    """Boxes of a few odd rows to several tiles of them, and tiles that move in
+    vectors for one element size and in windows for the other."""
+    jobs = []
+    for m in (RAGGED, ModelShape(LLAMA, 2, 60, 12, 12, 204, 60, 0, 1), ModelShape(GPT, 2, 24, 24, 24, 72, 48, 9, 1),
+              ModelShape(GPT, 2, 1224, 24, 24, 3624, 2424, 0, 0)):
+        for a, b in ((P(3, 1), P(2, 1)), (P(2, 1), P(3, 2)), (P(1, 1), P(6, 1)), (P(6, 1), P(1, 1))):
+            jobs.append(_args(m, a, b, False, "identity"))
+            jobs.append(_args(m, a, b, True, _oracle_sketch(m, a, b)))
+    _run_all(tilewalk, jobs)

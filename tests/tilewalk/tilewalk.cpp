@@ -1,12 +1,16 @@
 // tilewalk.cpp -- host replay of the copy kernels' walks over the copy
 // tables the planner builds (pack, unpack and Refer; all kinds at once, one
 // sub-chunk of each kind per workgroup; one kind at a time, kind_group(es)
-// sub-chunks of kind_sub_elems(es) elements per workgroup).  For every tile it checks that each row stays inside its arena,
-// message section or source arena, that vector accesses are 16-byte aligned,
-// that a sub-chunk needs no more lanes than a workgroup has, and that the
-// writes of a launch cover the target bytes exactly once: each message
-// (padding included) for a pack, each target piece for the unpack plus Refer
-// of one target.
+// sub-chunks of kind_sub_elems(es) elements per workgroup).  Tiles of whole
+// aligned vectors are walked in vectors, others in windows and their pieces, and
+// all-kinds launches in the order of their XCD runs, as the kernels do.  For
+// every tile it checks that each access stays inside its arena, message
+// section or source arena, that vectors are 16-byte aligned (of windows, the
+// target side, and of pieces each to its own size), that a sub-chunk needs no
+// more lanes than a workgroup has, and that the writes of a launch cover the
+// target bytes exactly once: each message (padding included) for a pack, each
+// target piece for the unpack plus Refer of one target.
+// Every device pointer is 256-byte aligned, so addresses here count from 0.
 //
 // Test code: it links the library's host planner and its tile geometry
 // header; it computes no expected values.
@@ -47,32 +51,92 @@ static uint64_t npad_of(const etc_plan_t& P, int s, int d) {
   return m ? m->npad : 0;
 }
 
-// Sort and merge one tile's write intervals, failing on any overlap.
-static std::vector<Iv> merge_tile(std::vector<Iv> w, const char* what) {
-  std::sort(w.begin(), w.end(), [](Iv a, Iv b) { return a.lo < b.lo; });
-  std::vector<Iv> m;
-  for (auto x : w) {
+// Sort and merge one tile's write intervals in place, failing on any overlap.
+static void merge_tile(std::vector<Iv>& w, const char* what) {
+  const auto before = [](Iv a, Iv b) { return a.lo < b.lo; };
+  if (!std::is_sorted(w.begin(), w.end(), before)) std::sort(w.begin(), w.end(), before);
+  size_t n = 0;  // merged so far
+  for (const Iv x : w) {
     if (x.hi == x.lo) continue;
-    if (!m.empty() && x.lo < m.back().hi) { FAIL("%s: sub-chunks of one tile overlap", what); continue; }
-    if (!m.empty() && m.back().hi == x.lo) m.back().hi = x.hi; else m.push_back(x);
+    if (n && x.lo < w[n - 1].hi) { FAIL("%s: sub-chunks of one tile overlap", what); continue; }
+    if (n && w[n - 1].hi == x.lo) w[n - 1].hi = x.hi; else w[n++] = x;
   }
-  return m;
+  w.resize(n);
+}
+
+// One kind of one tile: byte offsets of its first row on both sides, and what
+// bounds them.
+struct KindWalk {
+  uint64_t a0, m0, a_end, m_lo, m_end;  // arena side, message side (or source arena)
+  uint64_t a_ld, m_ld;                  // row pitches
+  bool pack;
+  int es, kind;
+  std::vector<Iv>& writes;
+
+  uint64_t to(uint32_t r) const { return pack ? m0 + r * m_ld : a0 + r * a_ld; }  // target side of row r
+  // elements [c0, c1) of row r, moved by one lane
+  void move(uint32_t r, int64_t c0, int64_t c1) {
+    const uint64_t alo = a0 + r * a_ld + c0 * es, mlo = m0 + r * m_ld + c0 * es, n = uint64_t(c1 - c0) * es;
+    if (alo + n > a_end) FAIL("arena OOB kind %d", kind);
+    if (mlo < m_lo || mlo + n > m_end) FAIL("message OOB kind %d", kind);
+    writes.push_back(pack ? Iv{mlo, mlo + n} : Iv{alo, alo + n});
+  }
+};
+
+// The vectors of sub-chunk j of a tile.
+static void walk_vectors(KindWalk& k, const TileGeom& g, uint32_t per, uint32_t j) {
+  const uint32_t vw = 16u / uint32_t(k.es), vpr = g.nc / vw;
+  if (per > kSubThreads) FAIL("a vector sub-chunk needs more lanes than threads");
+  if (g.nc % vw) FAIL("vector rows not whole vectors");
+  uint32_t lo, hi;
+  sub_range(j, per, g.nr * vpr, &lo, &hi);
+  if (lo >= hi) return;
+  for (uint32_t r = lo / vpr; lo < hi && r <= (hi - 1) / vpr; ++r) {
+    if ((k.a0 + r * k.a_ld) % 16 || (k.m0 + r * k.m_ld) % 16) FAIL("vector misaligned kind %d", k.kind);
+    k.move(r, int64_t(std::max(lo, r * vpr) - r * vpr) * vw, int64_t(std::min(hi, (r + 1) * vpr) - r * vpr) * vw);
+  }
+}
+
+// The windows of sub-chunk j of a tile, those of a second pass included.
+static void walk_windows(KindWalk& k, const TileGeom& g, uint32_t per, uint32_t j) {
+  const uint32_t vw = 16u / uint32_t(k.es), wpr = windows_per_row(g.nc, k.es), n = g.nr * wpr;
+  if (per > kSubThreads) FAIL("a sub-chunk of windows needs more lanes than threads");
+  for (uint32_t lane = 0; lane < per; ++lane)
+    for (uint32_t i = j * per + lane; i < n; i += lap_windows(k.es)) {
+      const uint32_t r = i / wpr;
+      const Window x = row_window(i - r * wpr, g.nc, k.to(r), k.es);
+      if (x.hi <= x.lo) continue;
+      const uint64_t at = k.to(r) + uint64_t(x.lo) * k.es;
+      const uint32_t m = uint32_t(x.hi - x.lo);
+      if (m == vw) {
+        if (at % 16) FAIL("window off its 16-byte unit");
+        k.move(r, x.lo, x.hi);
+        continue;
+      }
+      const bool inside = at % 16 && (at + uint64_t(m) * k.es) % 16;
+      const Pieces p = window_pieces(int32_t(m), uint32_t(at % 16) / uint32_t(k.es), k.es);
+      const struct { bool is; int32_t e, n; } pieces[3] = {{p.p4, p.e4, 4}, {p.p2, p.e2, 2}, {p.p1, p.e1, 1}};
+      for (const auto& q : pieces) {
+        if (!q.is) continue;
+        if (q.e < 0 || q.e + q.n > int32_t(m)) FAIL("a piece outside its window");
+        if (!inside && (at + uint64_t(q.e) * k.es) % (uint64_t(q.n) * k.es)) FAIL("piece misaligned");
+        k.move(r, x.lo + q.e, x.lo + q.e + q.n);
+      }
+    }
 }
 
 // Replay a launch as the kernels run it: for all four kinds, workgroup
 // t * kSubPerTile + j copies sub-chunk j (kSubElems elements) of every kind
-// of tile t; for one kind of es bytes, workgroup w of kind_grid(ntiles, es)
-// copies, when kind_wg_tile(w) gives it tile t and group q, its sub-chunks
-// [q * G, (q + 1) * G) of kind_sub_elems(es) elements, G = kind_group(es).
-// Either way every sub-chunk of every tile must be copied once per kind in
-// the launch.
+// of tile t, or the one that xcd_run gives in its place; for one kind of es
+// bytes, workgroup w of kind_grid(ntiles, es) copies, when kind_wg_tile(w)
+// gives it tile t and group q, its sub-chunks [q * G, (q + 1) * G) of
+// kind_sub_elems(es) elements, G = kind_group(es).
 static void replay_sub(const std::vector<CopyBox>& v, bool pack, bool sectioned, uint32_t kind_mask,
                        uint64_t arena_elems, const std::vector<uint64_t>& peer_bytes,
                        std::vector<std::vector<Iv>> W[4], std::vector<Iv> A[4], bool arenas) {
   const uint32_t nbox = uint32_t(v.size() - 1), ntiles = v.back().tile0;
   const bool all = kind_mask == 0xFu;
   const int kes = kind_mask == 1u ? 2 : 4;  // element size of a one-kind launch
-  const uint32_t per_tile = kSubPerTile;  // all-kinds launches
   const uint32_t sub_elems = all ? kSubElems : kind_sub_elems(kes);
   const uint32_t subs_per_tile = kTileElems / sub_elems;
   // one-kind launches: the groups each tile receives, from the whole grid
@@ -89,7 +153,10 @@ static void replay_sub(const std::vector<CopyBox>& v, bool pack, bool sectioned,
       groups_of[t].push_back(q);
     }
   }
-  if (uint64_t(ntiles) * per_tile > uint64_t(INT32_MAX)) { FAIL("grid over 2^31 - 1 workgroups"); return; }
+  if (uint64_t(ntiles) * kSubPerTile > uint64_t(INT32_MAX)) { FAIL("grid over 2^31 - 1 workgroups"); return; }
+  std::vector<uint32_t> subs;
+  std::vector<char> seen;
+  std::vector<Iv> writes;
   for (uint32_t t = 0; t < ntiles; ++t) {
     const uint32_t bi = box_of_tile(v.data(), nbox, t);  // the same for every j of the tile
     if (bi >= nbox) { FAIL("tile past last box"); return; }
@@ -97,66 +164,62 @@ static void replay_sub(const std::vector<CopyBox>& v, bool pack, bool sectioned,
     const TileGeom g = tile_geom(b, t, v[bi + 1].tile0);
     if (g.nr == 0 || g.nc == 0 || g.r0 >= b.rows || g.c0 >= b.cols) FAIL("empty/outside tile");
     if (!arenas && b.peer >= peer_bytes.size()) { FAIL("peer slot %u out of range", b.peer); return; }
+    if (!arenas && b.m_ld != b.cols) FAIL("message box with a row stride");
+    if (arenas && (b.pad || b.msg_npad)) FAIL("refer box with padding");
+    // the sub-chunks of tile t that its workgroups copy
+    subs.clear();
+    if (all) {
+      for (uint32_t w = t * kSubPerTile; w < (t + 1) * kSubPerTile; ++w) subs.push_back(w % kSubPerTile);
+    } else {
+      for (uint32_t q : groups_of[t])
+        for (uint32_t i = 0; i < kind_group(kes); ++i) subs.push_back(q * kind_group(kes) + i);
+    }
+    seen.assign(subs_per_tile, 0);
+    for (uint32_t j : subs)
+      if (j >= subs_per_tile || seen[j]++) FAIL("sub-chunk %u of tile %u copied twice or out of range", j, t);
+    if (subs.size() != subs_per_tile) FAIL("tile %u: %zu sub-chunks copied, %u in the tile", t, subs.size(),
+                                           subs_per_tile);
+    const bool vectors = sub_vectors(b, g, 2) && sub_vectors(b, g, 4);  // all-kinds: the tile's every kind
+    const uint32_t used = sub_used(g);
     for (int k = 0; k < 4; ++k) {
       if (!(kind_mask & (1u << k))) continue;
       const int es = k == 0 ? 2 : 4;
-      const uint64_t ae = tile_arena_elem(b, g), me = tile_msg_elem(b, g);
+      if (!all && es != kes) FAIL("one-kind launch of another element size");
       const uint64_t sec = (sectioned && !arenas) ? section_byte(b.msg_npad, k) : 0;
-      const uint64_t sec_end = arenas ? peer_bytes[k] : sec + b.msg_npad * es;
-      const uint64_t sp = (pack ? uint64_t(b.a_ld) : b.m_ld) * es, dp = (pack ? b.m_ld : uint64_t(b.a_ld)) * es;
-      if (!arenas && b.m_ld != b.cols) FAIL("message box with a row stride");
-      if (arenas && (b.pad || b.msg_npad)) FAIL("refer box with padding");
-      if (std::max(sp, dp) * (g.nr - 1) + uint64_t(g.nc) * es >= (1ull << 31)) FAIL("tile extent over 2^31");
+      const uint64_t sec_end = arenas ? peer_bytes[k] : std::min(sec + b.msg_npad * es, peer_bytes[b.peer]);
+      KindWalk w{tile_arena_elem(b, g) * es, sec + tile_msg_elem(b, g) * es, arena_elems * es, sec, sec_end,
+                 uint64_t(b.a_ld) * es, b.m_ld * es, pack, es, k, writes};
+      writes.clear();
+      if (std::max(w.a_ld, w.m_ld) * (g.nr - 1) + uint64_t(g.nc) * es >= (1ull << 31)) FAIL("tile extent over 2^31");
       const bool vk = sub_vectors(b, g, es);
-      const uint32_t unit = vk ? 16u / uint32_t(es) : 1u;  // elements per item
-      const uint32_t per = sub_elems / unit;               // items per sub-chunk
-      const uint32_t ipr = g.nc / unit;                    // items per row
       if (!vk && g.nr > 1 && g.nr * windows_per_row(g.nc, es) > kTileElems / (16u / uint32_t(es)))
         FAIL("a tile of %u rows of %u elements has windows for a second pass", g.nr, g.nc);
-      if (vk && per > kSubThreads) FAIL("a vector sub-chunk needs more lanes than threads");
-      if (!all && es != kes) FAIL("one-kind launch of another element size");
-      if (vk && g.nc % unit) FAIL("vector rows not whole vectors");
-      std::vector<Iv> tw;
-      // the sub-chunks of tile t, in the order and with the index arithmetic
-      // of the kernels' workgroups
-      std::vector<uint32_t> subs;
-      if (all) {
-        for (uint32_t w = t * per_tile; w < (t + 1) * per_tile; ++w) {
-          if (w / kSubPerTile != t) FAIL("workgroup %u maps to another tile", w);
-          subs.push_back(w % kSubPerTile);
-        }
-      } else {
-        const uint32_t grp = kind_group(kes);
-        for (uint32_t q : groups_of[t])
-          for (uint32_t i = 0; i < grp; ++i) subs.push_back(q * grp + i);
-      }
-      std::vector<char> seen(subs_per_tile, 0);
-      for (uint32_t j : subs) {
-        if (j >= subs_per_tile || seen[j]++) FAIL("sub-chunk %u of tile %u copied twice or out of range", j, t);
-      }
-      if (subs.size() != subs_per_tile) FAIL("tile %u: %zu sub-chunks copied, %u in the tile", t, subs.size(),
-                                             subs_per_tile);
+      const uint32_t per = sub_elems / (16u / uint32_t(es));  // vectors or windows per sub-chunk
+      // whether every row starts on a line on both sides
+      const bool lines = ((w.a0 | w.m0 | (g.nr == 1 ? 0 : w.a_ld | w.m_ld)) % kLineBytes) == 0;
+      bool padded = false;
       for (uint32_t j : subs) {
         if (j >= subs_per_tile) continue;
-        uint32_t lo, hi;
-        sub_range(j, per, g.nr * ipr, &lo, &hi);
-        for (uint32_t r = lo / (ipr ? ipr : 1); lo < hi && r <= (hi - 1) / ipr; ++r) {
-          const uint32_t c0 = std::max(lo, r * ipr) - r * ipr, c1 = std::min(hi, (r + 1) * ipr) - r * ipr;
-          const uint64_t abase = (ae + uint64_t(r) * b.a_ld) * es, mbase = sec + (me + uint64_t(r) * b.m_ld) * es;
-          const uint64_t alo = abase + uint64_t(c0) * unit * es, ahi = abase + uint64_t(c1) * unit * es;
-          const uint64_t mlo = mbase + uint64_t(c0) * unit * es, mhi = mbase + uint64_t(c1) * unit * es;
-          if (ahi > arena_elems * es) FAIL("arena OOB kind %d", k);
-          if ((!arenas && mhi > peer_bytes[b.peer]) || mhi > sec_end) FAIL("message OOB peer %u kind %d", b.peer, k);
-          if (vk && (abase % 16 || mbase % 16)) FAIL("vector misaligned kind %d", k);
-          tw.push_back(pack ? Iv{mlo, mhi} : Iv{alo, ahi});
+        uint32_t run = j;
+        if (all && vectors) {
+          if (!(b.vec & kLineBox)) run = xcd_run(j, (g.nr * g.nc + kSubElems - 1) / kSubElems);
+          if ((b.vec & kLineBox) && es == 4 && !lines) FAIL("a box marked as on lines is not");
+        } else if (all) {
+          if (j >= used) continue;
+          if (!lines) run = xcd_run(j, used);
         }
+        if (j == 0 && pack && g.last && b.pad && !(all && vectors)) padded = true;
+        if (vk) walk_vectors(w, g, per, run);
+        else walk_windows(w, g, per, run);
       }
-      if (pack && g.last && b.pad) {
+      if (pack && g.last && b.pad && !padded) FAIL("the padding after a box is not written");
+      if (padded) {
         const uint64_t plo = sec + (b.m_off + uint64_t(b.rows) * b.cols) * es, phi = plo + uint64_t(b.pad) * es;
         if (phi > sec_end) FAIL("pad overrun");
-        tw.push_back({plo, phi});
+        w.writes.push_back({plo, phi});
       }
-      for (auto x : merge_tile(tw, "sub-chunk walk")) {
+      merge_tile(w.writes, "sub-chunk walk");
+      for (auto x : w.writes) {
         if (pack) W[k][b.peer].push_back(x); else A[k].push_back(x);
       }
     }
