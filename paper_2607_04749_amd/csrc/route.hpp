@@ -32,12 +32,6 @@ __host__ __device__ inline int64_t unit_elems(const RouteTensor& t) {
   return t.split == kRows ? t.cols : t.split == kCols ? t.rows : t.rows * t.cols;
 }
 
-__host__ __device__ inline Span shard_span(const RouteTensor& t, int tp, int TP) {
-  if (t.split == kRepl) return Span{0, 1};
-  const int64_t w = split_extent(t) / TP;
-  return Span{tp * w, (tp + 1) * w};
-}
-
 // copy role of the tensor held on stage pp (a stage holds at most one role)
 __host__ __device__ inline int role_on(const int32_t stage[2], int pp) {
   return stage[0] == pp ? 0 : (stage[1] == pp ? 1 : -1);
@@ -131,22 +125,6 @@ __host__ __device__ inline bool sends_shard(const SourceAt& a, const TargetAt& b
     if (best_role >= 0) return rep * pt + best_pp * c.tps + best_tp == a.s;
   }
   return false;
-}
-
-// Range of the split dim that source s sends to target d for tensor t (empty
-// when s sends nothing).
-__host__ __device__ inline Span routed_span(const RouteTensor& t, int s, int d, int home,
-                                            const RouteCtx& c) {
-  const Span none{0, 0};
-  const SourceAt a = source_at(s, c);
-  const TargetAt b = target_at(d, home, c);
-  const int role_d = role_on(t.dst_stage, b.pp);
-  if (role_d < 0 || a.dead || role_on(t.src_stage, a.pp) < 0) return none;
-  const Span need = shard_span(t, b.tp, c.tpd);
-  const Span have = shard_span(t, a.tp, c.tps);
-  const Span x{have.lo > need.lo ? have.lo : need.lo, have.hi < need.hi ? have.hi : need.hi};
-  if (x.len() == 0 || !sends_shard(a, b, t.src_stage, t.split == kRepl, role_d, c)) return none;
-  return x;
 }
 
 }  // namespace etc

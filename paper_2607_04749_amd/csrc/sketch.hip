@@ -8,7 +8,8 @@
 // k <= 128 of a PP x TP grid.  While rows are added, 0 <= u[i] <= the largest
 // entry (a free column has potential 0) and -(largest entry) <= v[j] <= 0, so
 // sums stay below four times the largest entry: 64-bit where that fits, else
-// 128-bit.  Potentials change once per row added, not on every step of its tree.
+// 128-bit (a host-only plan with 2^59 bytes on a rank; etc_sketch takes entries
+// up to 2^52).  Potentials change once per row added, not on every step of its tree.
 // Two assignments of 64 x 32 entries, one core: about 700 us with 128-bit
 // potentials updated on every step, 180 us this way.
 #include <algorithm>

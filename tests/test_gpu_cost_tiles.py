@@ -1,8 +1,9 @@
 """The cost kernel covers a matrix in tiles of up to 256 columns and 32 rows:
 all four matrices against the oracle where a tile is cut (one row or column,
 one column past a tile, rows that do not fill the last tile), with several
-replicas, tied embeddings on two stages, and failed ranks whose stand-ins lie
-one and two replicas on."""
+replicas, tied embeddings on two stages, many stages on one side, failed ranks
+whose stand-ins lie one and two replicas on, and replicas that lost a rank in
+any of their words of the bitmap."""
 import numpy as np
 import pytest
 
@@ -27,6 +28,10 @@ UNTIED16 = ModelShape(LLAMA, 16, 24, 12, 12, 36, 24, 0, 0)
     (UNTIED, P(4, 4, 16), P(4, 4, 33), [31, 32]),
     (UNTIED, P(1, 4, 64), P(2, 2, 64), list(range(8))),
     (TIED, P(2, 1, 4), P(1, 2, 7), [6, 0, 1]),  # stand-ins past the last replica
+    # the only lost rank of a replica in a later word of the bitmap than its first: ranks 0 to 63, and 30 to 35
+    (UNTIED16, P(4, 16, 2), P(4, 8, 2), [40]),
+    (TIED16, P(4, 16, 2), P(2, 16, 3), [63, 97]),
+    (UNTIED, P(3, 2, 7), P(2, 2, 7), [33]),
     (TIED16, P(1, 16, 1), P(1, 1, 1), []),  # many source stages of one target stage
     (TIED16, P(2, 1, 2), P(1, 16, 3), [1]),
     (UNTIED16, P(2, 16, 3), P(4, 2, 2), [5, 40]),

@@ -1,5 +1,5 @@
-"""The planner's routing and COST in closed form against the rules asked tensor
-by tensor, on the host (tests/tilewalk/routes.cpp)."""
+"""The planner's routing and COST in closed form against the rules, written out
+on their own and asked tensor by tensor, on the host (tests/tilewalk/routes.cpp)."""
 import os
 import subprocess
 

@@ -11,7 +11,7 @@ import oracle
 from helpers import empty_arenas, host_arenas, rank_elems
 from micro import MICRO_MODELS, cfg_pairs, layers_only
 from paper_2607_04749_amd import etc
-from paper_2607_04749_amd.workloads import WORKLOADS, Parallel
+from paper_2607_04749_amd.workloads import LLAMA, WORKLOADS, ModelShape, Parallel
 
 HOST = etc.PLAN_HOST_ONLY
 
@@ -283,3 +283,14 @@ def test_sketch_total_range():
     with pytest.raises(etc.EtcError) as e:
         etc.etc_sketch(np.full((2, 2), (1 << 52) + 1, np.uint64))
     assert e.value.code == etc.ERR_UNSUPPORTED
+
+
+def test_plan_past_the_64_bit_sketch():
+    """Costs of 2^59 and more are matched in 128 bits.  Only a host-only plan
+    gets there (etc_sketch takes entries up to 2^52): 64 layers of hidden 2^25,
+    2^60 bytes on a rank.  Pairs that move 2^50 bytes or more count as unpaired,
+    so of two stages that become four, the two that hold all they need stay."""
+    m = ModelShape(LLAMA, 64, 1 << 25, 64, 64, 1 << 26, 1 << 25, 0, 0)
+    plan = etc.etc_plan(m, Parallel(1, 2), Parallel(1, 4), flags=HOST | etc.PLAN_SKETCH)
+    assert 14 * plan.arena_elems(etc.SIDE_DST, 0) > 1 << 59
+    assert plan.pairing().tolist() == [0, -1, 1, -1]

@@ -1,11 +1,13 @@
 // routes.cpp -- the planner's sender lists in LCM slices against the routing
-// rule asked tensor by tensor (routed_span), its closed-form COST against
-// sums over the tensors, and the sketch in 64-bit against 128-bit whole numbers, on
-// seeded configurations: tied and untied, uneven TP and PP degrees, replicas,
-// failed ranks, pairings of every sort.  Prints "ok".
+// rule, written out here on its own and asked tensor by tensor, its closed-form
+// COST against sums over the tensors, the cost kernel's tables against the
+// tensors, and the sketch in 64-bit against 128-bit whole numbers, on seeded
+// configurations: tied and untied, uneven TP and PP degrees, replicas,
+// failed ranks, pairings of every sort.  Prints "ok".  Test code.
 #include <algorithm>
 #include <cstdio>
 #include <random>
+#include <tuple>
 #include <vector>
 #include "etc_internal.hpp"
 #include "plan.hpp"
@@ -15,6 +17,50 @@ using namespace etc;
 static int errors = 0;
 static void expect(bool ok, const char* what, int it) {
   if (!ok && errors++ < 20) printf("configuration %d: %s\n", it, what);
+}
+
+// The range of its split dim that a rank with TP rank tp of TP holds of t.
+static Span shard_span(const RouteTensor& t, int tp, int TP) {
+  if (t.split == kRepl) return Span{0, 1};
+  const int64_t w = split_extent(t) / TP;
+  return Span{tp * w, (tp + 1) * w};
+}
+
+// The copy role in which a stage holds a tensor, or -1.
+static int role_of(const int32_t stage[2], int pp) { return stage[0] == pp ? 0 : stage[1] == pp ? 1 : -1; }
+
+// The source that the rule names for the part of t that target d shares with
+// source s's shard, or -1: the paired source where it holds that part; else the
+// live holder, in the first replica from the serving one on that has any, of d's
+// own copy role, of the TP rank congruent to d's, of the lowest stage, of the
+// lowest TP rank, in this order.
+static int sender(const etc_plan_t& P, const std::vector<char>& dead, const RouteTensor& t, int s, int d) {
+  const int Sr = P.src.replica_size(), home = P.home[d];
+  const auto holds = [&](int x) {
+    return !dead[x] && role_of(t.src_stage, P.src.pp_of(x)) >= 0 &&
+           (t.split == kRepl || P.src.tp_of(x) == P.src.tp_of(s));
+  };
+  if (home >= 0 && holds(home)) return home;
+  const int role_d = role_of(t.dst_stage, P.dst.pp_of(d));
+  for (int i = 0; i < P.src.dp; ++i) {
+    const int rep = (P.dst.replica(d) + i) % P.src.dp;
+    std::vector<std::tuple<bool, bool, int, int, int>> live;
+    for (int x = rep * Sr; x < (rep + 1) * Sr; ++x)
+      if (holds(x))
+        live.emplace_back(role_of(t.src_stage, P.src.pp_of(x)) != role_d,
+                          P.src.tp_of(x) != P.dst.tp_of(d) % P.src.tp, P.src.pp_of(x), P.src.tp_of(x), x);
+    if (!live.empty()) return std::get<4>(*std::min_element(live.begin(), live.end()));
+  }
+  return -1;
+}
+
+// The range of t's split dim that source s sends to target d.
+static Span routed(const etc_plan_t& P, const std::vector<char>& dead, const RouteTensor& t, int s, int d) {
+  if (role_of(t.dst_stage, P.dst.pp_of(d)) < 0 || role_of(t.src_stage, P.src.pp_of(s)) < 0 || dead[s])
+    return Span{0, 0};
+  const Span need = shard_span(t, P.dst.tp_of(d), P.dst.tp), have = shard_span(t, P.src.tp_of(s), P.src.tp);
+  const Span x{std::max(have.lo, need.lo), std::min(have.hi, need.hi)};
+  return x.len() && sender(P, dead, t, s, d) == s ? x : Span{0, 0};
 }
 
 int main() {
@@ -63,10 +109,10 @@ int main() {
       for (int s = 0; s < Sr; ++s) {
         uint64_t need = 0, ov = 0;
         for (const RouteTensor& t : P.route_tensors) {
-          if (role_on(t.dst_stage, P.dst.pp_of(d)) < 0) continue;
+          if (role_of(t.dst_stage, P.dst.pp_of(d)) < 0) continue;
           const Span want = shard_span(t, P.dst.tp_of(d), P.dst.tp), have = shard_span(t, P.src.tp_of(s), P.src.tp);
           need += uint64_t(want.len() * unit_elems(t));
-          if (role_on(t.src_stage, P.src.pp_of(s)) < 0) continue;
+          if (role_of(t.src_stage, P.src.pp_of(s)) < 0) continue;
           ov += uint64_t(Span{std::max(have.lo, want.lo), std::min(have.hi, want.hi)}.len() * unit_elems(t));
         }
         expect(cost[size_t(d) * Sr + s] == (need - ov) * 14, "COST differs from the sum over the tensors", it);
@@ -82,7 +128,7 @@ int main() {
         const CostPair p = at < st.n ? table.pairs[st.first + at] : CostPair{};
         uint64_t held = 0, held1 = 0, listed = 0;  // elements per LCM slice, or of a whole tensor
         for (const RouteTensor& t : P.route_tensors) {
-          if (role_on(t.dst_stage, pd) < 0 || role_on(t.src_stage, ps) < 0) continue;
+          if (role_of(t.dst_stage, pd) < 0 || role_of(t.src_stage, ps) < 0) continue;
           const uint64_t n = uint64_t(unit_elems(t)) *
                              (t.split == kRepl ? 1 : split_extent(t) / (lcm_slices(P).src * P.src.tp));
           held += n;
@@ -91,7 +137,7 @@ int main() {
         for (uint32_t i = p.first; i < p.end; ++i) {
           const CostGroup& g = table.groups[i];
           listed += g.slice + g.whole;
-          expect(role_on(g.src_stage, ps) >= 0, "a group of another source stage", it);
+          expect(role_of(g.src_stage, ps) >= 0, "a group of another source stage", it);
           for (uint32_t k = p.first; k < i; ++k)
             expect(g.role_d != table.groups[k].role_d || g.src_stage[0] != table.groups[k].src_stage[0] ||
                        g.src_stage[1] != table.groups[k].src_stage[1], "a group listed twice", it);
@@ -119,7 +165,6 @@ int main() {
     }
     planned += recoverable;
     // every box, in the order of d's arena and of the sources
-    const RouteCtx c = host_route_ctx(P);
     bool whole = true;
     for (int d = 0; d < D; ++d) {
       std::vector<size_t> at(S, 0);
@@ -129,7 +174,7 @@ int main() {
         const RouteTensor& t = P.route_tensors[q.tensor];
         uint64_t got = 0;
         for (int s = 0; s < S; ++s) {
-          const Span x = routed_span(t, s, d, P.home[d], c);
+          const Span x = routed(P, dead, t, s, d);
           got += uint64_t(x.len() * unit_elems(t));
           if (x.len() == 0 || !recoverable) continue;
           const bool keep = (P.flags & ETC_PLAN_DIRECT_REFER) && s == P.home[d];
