@@ -4,7 +4,7 @@
 // between a rank's four state arenas (strided rows) and message sections
 // (contiguous rows), for all four state kinds, or (Refer) straight from a
 // source rank's arenas into a target rank's.  Boxes are pre-cut on the host
-// into uniform tiles of kTileElems elements per kind.
+// into uniform tiles of up to kTileElems elements per kind.
 //
 // Launch shape: short-lived one-wavefront workgroups (kSubThreads threads)
 // over sub-chunks of the tiles, kSubElems elements of a kind each (1 KB of an
@@ -36,9 +36,12 @@
 // memory, twice, as neighbouring workgroups lie on different XCDs.  With four
 // consecutive KB per XCD (xcd_run) these became 6.25, 5.85 and 5.7, so boxes
 // off the lines take their sub-chunks in that order; boxes on them do not,
-// which would cost 1.7 %.  Against element-by-element copies, in one process:
-// a 1.9 B GPT from TP4 to TP6 (rows of 597 elements) 940 -> 850 us, other
-// shapes with odd widths 9 to 17 % less time, one kind at a time 10 to 12 %.
+// which would cost 1.7 %.  Against element-by-element copies on the same
+// buffers, GPU time: a 1.9 B GPT from TP4 to TP6 (rows of 597 elements) 933 ->
+// 798 us; a 6-layer Llama from TP3 to TP2 (rows of 681 and 454) 69.6 -> 62.9;
+// unpacks from TP8 to TP6 with boxes of 7, 27 and 101 columns 67 -> 53, 34 ->
+// 29 and 148 -> 127, and the same steps one kind at a time 236 -> 155, 198 ->
+// 94 and 399 -> 257.
 #include <hip/hip_runtime.h>
 
 #include "copy_desc.hpp"
@@ -80,6 +83,10 @@ struct KindTile {
     sld = (kPack ? uint64_t(b.a_ld) : b.m_ld) * kEs;
     dld = (kPack ? b.m_ld : uint64_t(b.a_ld)) * kEs;
   }
+  __device__ __forceinline__ const E* from(uint32_t r, uint32_t c) const {
+    return reinterpret_cast<const E*>(src + r * sld) + c;
+  }
+  __device__ __forceinline__ E* to(uint32_t r, uint32_t c) const { return reinterpret_cast<E*>(dst + r * dld) + c; }
   // zero the padding that rounds the box up to a multiple of 8 elements
   __device__ __forceinline__ void zero_pad(const CopyBox& b) const {
     E* tail = reinterpret_cast<E*>(Mb + (b.m_off + uint64_t(b.rows) * b.cols) * kEs);
@@ -91,7 +98,7 @@ struct KindTile {
 // of a wavefront's loads are issued before any store: most wavefronts hold an
 // end of some row, and a second load after the first store would double their
 // time.  (Rows inside one 16-byte unit went element by element, a load and a
-// store in turn: tiny boxes of 5-wide rows 3 to 5 % slower than in pieces.)
+// store in turn: tiny boxes of 5-wide rows 4 to 5 % slower than in pieces.)
 template <int kEs>
 __device__ __forceinline__ void copy_window(const char* src, char* dst, uint32_t w, uint32_t nc) {
   using E1 = typename std::conditional<kEs == 2, uint16_t, uint32_t>::type;
@@ -172,6 +179,30 @@ __device__ __forceinline__ void copy_sub_any(const KindTile<kPack, kEs>& k, cons
     }
 }
 
+// All four kinds of a tile of at most one element per lane: the loads of all
+// kinds before any store, and no windows to work out.  In windows such tiles took
+// longer than element by element: 400 layers of hidden 6 and 10, unpack 196 and
+// 200 us (180 and 189 by elements), 137 and 150 this way.
+template <bool kPack>
+__device__ __forceinline__ void copy_few(const CopyArgs& a, const CopyBox& b, char* mbase, const TileGeom& g) {
+  const KindTile<kPack, 2> k0(a, b, mbase, g, 0);
+  const KindTile<kPack, 4> k1(a, b, mbase, g, 1), k2(a, b, mbase, g, 2), k3(a, b, mbase, g, 3);
+  if (kPack && g.last && b.pad) {
+    k0.zero_pad(b);
+    k1.zero_pad(b);
+    k2.zero_pad(b);
+    k3.zero_pad(b);
+  }
+  if (threadIdx.x >= g.nr * g.nc) return;
+  const uint32_t r = g.nr == 1 ? 0 : threadIdx.x / g.nc, c = threadIdx.x - r * g.nc;
+  const uint16_t v0 = *k0.from(r, c);
+  const uint32_t v1 = *k1.from(r, c), v2 = *k2.from(r, c), v3 = *k3.from(r, c);
+  *k0.to(r, c) = v0;
+  *k1.to(r, c) = v1;
+  *k2.to(r, c) = v2;
+  *k3.to(r, c) = v3;
+}
+
 template <bool kPack>
 __global__ __launch_bounds__(kSubThreads) void copy_sub_kernel(CopyArgs a) {
   const uint32_t t = blockIdx.x / kSubPerTile;
@@ -186,6 +217,10 @@ __global__ __launch_bounds__(kSubThreads) void copy_sub_kernel(CopyArgs a) {
     copy_sub<kPack, 4, kSubElems>(a, b, mbase, g, j, 1);
     copy_sub<kPack, 4, kSubElems>(a, b, mbase, g, j, 2);
     copy_sub<kPack, 4, kSubElems>(a, b, mbase, g, j, 3);
+    return;
+  }
+  if (tile_few(g)) {
+    if (j == 0) copy_few<kPack>(a, b, mbase, g);
     return;
   }
   const uint32_t used = sub_used(g);

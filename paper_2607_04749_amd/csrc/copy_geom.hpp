@@ -143,6 +143,8 @@ __host__ __device__ inline uint32_t windows_per_row(uint32_t nc, int es) {
   const uint32_t g = window_group(nc, es);
   return (nc * uint32_t(es) + 2 * g - 1 - uint32_t(es)) / g * (g / 16u);
 }
+// Whether an all-kinds launch copies a tile that moves in windows one element per lane.
+__host__ __device__ inline bool tile_few(const TileGeom& g) { return g.nr * g.nc <= kSubThreads; }
 // Windows in one pass of a tile's sub-chunks.  Tiles of several rows hold no
 // more (tiles.hip); a one-row tile may, and the first sub-chunks then take
 // the rest in a second pass.

@@ -125,6 +125,14 @@ static void walk_windows(KindWalk& k, const TileGeom& g, uint32_t per, uint32_t 
     }
 }
 
+// A tile of at most one element per lane.
+static void walk_few(KindWalk& k, const TileGeom& g) {
+  for (uint32_t lane = 0; lane < kSubThreads && lane < g.nr * g.nc; ++lane) {
+    const uint32_t r = g.nr == 1 ? 0 : lane / g.nc;
+    k.move(r, lane - r * g.nc, lane - r * g.nc + 1);
+  }
+}
+
 // Replay a launch as the kernels run it: for all four kinds, workgroup
 // t * kSubPerTile + j copies sub-chunk j (kSubElems elements) of every kind
 // of tile t, or the one that xcd_run gives in its place; for one kind of es
@@ -204,12 +212,15 @@ static void replay_sub(const std::vector<CopyBox>& v, bool pack, bool sectioned,
         if (all && vectors) {
           if (!(b.vec & kLineBox)) run = xcd_run(j, (g.nr * g.nc + kSubElems - 1) / kSubElems);
           if ((b.vec & kLineBox) && es == 4 && !lines) FAIL("a box marked as on lines is not");
-        } else if (all) {
+        } else if (all && !tile_few(g)) {
           if (j >= used) continue;
           if (!lines) run = xcd_run(j, used);
+        } else if (all && j) {
+          continue;
         }
         if (j == 0 && pack && g.last && b.pad && !(all && vectors)) padded = true;
-        if (vk) walk_vectors(w, g, per, run);
+        if (all && !vectors && tile_few(g)) walk_few(w, g);
+        else if (vk) walk_vectors(w, g, per, run);
         else walk_windows(w, g, per, run);
       }
       if (pack && g.last && b.pad && !padded) FAIL("the padding after a box is not written");
