@@ -100,11 +100,11 @@ struct KindTile {
 // time.  (Rows inside one 16-byte unit went element by element, a load and a
 // store in turn: tiny boxes of 5-wide rows 4 to 5 % slower than in pieces.)
 template <int kEs>
-__device__ __forceinline__ void copy_window(const char* src, char* dst, uint32_t w, uint32_t nc) {
+__device__ __forceinline__ void copy_window(const char* src, char* dst, uint32_t w, uint32_t nc, uint32_t group) {
   using E1 = typename std::conditional<kEs == 2, uint16_t, uint32_t>::type;
   using E2 = typename std::conditional<kEs == 2, uint32_t, uint64_t>::type;
   constexpr int32_t vw = 16 / kEs;
-  const Window x = row_window(w, nc, reinterpret_cast<uint64_t>(dst), kEs);
+  const Window x = row_window(w, nc, reinterpret_cast<uint64_t>(dst), kEs, group);
   const int32_t m = x.hi > x.lo ? x.hi - x.lo : 0;
   src += int64_t(x.lo) * kEs;
   dst += int64_t(x.lo) * kEs;
@@ -161,7 +161,7 @@ __device__ __forceinline__ void copy_sub(const CopyArgs& a, const CopyBox& b, ch
 // not start on 128-byte lines, sub-chunk `run` in its place.
 template <bool kPack, int kEs, uint32_t kSub>
 __device__ __forceinline__ void copy_sub_any(const KindTile<kPack, kEs>& k, const CopyBox& b, const TileGeom& g,
-                                             uint32_t j, uint32_t run) {
+                                             uint32_t j, uint32_t run, uint32_t group) {
   if (kPack && j == 0 && g.last && b.pad) k.zero_pad(b);
   const uint64_t bases = reinterpret_cast<uint64_t>(k.dst) | reinterpret_cast<uint64_t>(k.src);
   if ((bases | (g.nr == 1 ? 0 : k.dld | k.sld)) % kLineBytes != 0) j = run;
@@ -171,11 +171,11 @@ __device__ __forceinline__ void copy_sub_any(const KindTile<kPack, kEs>& k, cons
   }
   // windows [j * per, (j + 1) * per), and in a one-row tile the same windows of the next lap
   constexpr uint32_t per = kSub / (16 / kEs), lap = lap_windows(kEs);
-  const uint32_t wpr = windows_per_row(g.nc, kEs), n = g.nr * wpr;
+  const uint32_t wpr = windows_per_row(g.nc, kEs, group), n = g.nr * wpr;
   if (threadIdx.x < per)
     for (uint32_t i = j * per + threadIdx.x; i < n; i += lap) {
       const uint32_t r = g.nr == 1 ? 0 : i / wpr;
-      copy_window<kEs>(k.src + r * k.sld, k.dst + r * k.dld, i - r * wpr, g.nc);
+      copy_window<kEs>(k.src + r * k.sld, k.dst + r * k.dld, i - r * wpr, g.nc, group);
     }
 }
 
@@ -226,10 +226,10 @@ __global__ __launch_bounds__(kSubThreads) void copy_sub_kernel(CopyArgs a) {
   const uint32_t used = sub_used(g);
   if (j >= used) return;
   const uint32_t run = xcd_run(j, used);
-  copy_sub_any<kPack, 2, kSubElems>(KindTile<kPack, 2>(a, b, mbase, g, 0), b, g, j, run);
+  copy_sub_any<kPack, 2, kSubElems>(KindTile<kPack, 2>(a, b, mbase, g, 0), b, g, j, run, window_group(g.nc, 2));
 #pragma unroll 1  // one body for the three kinds: code that a small launch has to fetch
   for (int kind = 1; kind < 4; ++kind)
-    copy_sub_any<kPack, 4, kSubElems>(KindTile<kPack, 4>(a, b, mbase, g, kind), b, g, j, run);
+    copy_sub_any<kPack, 4, kSubElems>(KindTile<kPack, 4>(a, b, mbase, g, kind), b, g, j, run, window_group(g.nc, 4));
 }
 
 // ---------------------------------------------------------------------------
@@ -254,8 +254,9 @@ __global__ __launch_bounds__(kSubThreads) void copy_kind_kernel(CopyArgs a) {
     for (uint32_t i = 0; i < grp; ++i) copy_sub_vectors<kPack, kEs, sub>(k, g, q * grp + i);
     return;
   }
+  const uint32_t group = kind_window_group(g, kEs);
 #pragma unroll 1
-  for (uint32_t i = 0; i < grp; ++i) copy_sub_any<kPack, kEs, sub>(k, b, g, q * grp + i, q * grp + i);
+  for (uint32_t i = 0; i < grp; ++i) copy_sub_any<kPack, kEs, sub>(k, b, g, q * grp + i, q * grp + i, group);
 }
 
 // LDS reserved per workgroup and never touched, in all-kinds launches: with

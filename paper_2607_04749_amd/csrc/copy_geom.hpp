@@ -131,17 +131,17 @@ __host__ __device__ inline void sub_range(uint32_t j, uint32_t per, uint32_t n, 
 // smaller pieces.  Every row has windows_per_row of them, a few before its
 // start and past its end empty.  Groups of 16 and of 128 bytes measured up to
 // 3 % slower (rows of 1443 to 3813 elements) and 4 % slower (597 elements).
-// Rows of less than 512 bytes go without the grouping: most of their windows
-// would be empty (a row of 3 elements has 2 windows, or 8 in a group).  Packs
-// and unpacks with rows of 7 to 113 elements took 1 to 15 % less time that
-// way, 1 to 4 % less than with the line at 128 bytes and as much as at 256.
+// All-kinds launches, which have workgroups in plenty, go without the grouping
+// for rows of less than 512 bytes: most of their windows would be empty (a row
+// of 3 elements has 2 windows, or 8 in a group).  Packs and unpacks with rows
+// of 7 to 113 elements took 1 to 15 % less time that way, 1 to 4 % less than
+// with the line at 128 bytes and as much as at 256.
 constexpr uint32_t kSectorBytes = 64, kNarrowBytes = 512;
 __host__ __device__ inline uint32_t window_group(uint32_t nc, int es) {
   return nc * uint32_t(es) < kNarrowBytes ? 16u : kSectorBytes;
 }
-__host__ __device__ inline uint32_t windows_per_row(uint32_t nc, int es) {
-  const uint32_t g = window_group(nc, es);
-  return (nc * uint32_t(es) + 2 * g - 1 - uint32_t(es)) / g * (g / 16u);
+__host__ __device__ inline uint32_t windows_per_row(uint32_t nc, int es, uint32_t group) {
+  return (nc * uint32_t(es) + 2 * group - 1 - uint32_t(es)) / group * (group / 16u);
 }
 // Whether an all-kinds launch copies a tile that moves in windows one element per lane.
 __host__ __device__ inline bool tile_few(const TileGeom& g) { return g.nr * g.nc <= kSubThreads; }
@@ -149,10 +149,18 @@ __host__ __device__ inline bool tile_few(const TileGeom& g) { return g.nr * g.nc
 // more (tiles.hip); a one-row tile may, and the first sub-chunks then take
 // the rest in a second pass.
 __host__ __device__ constexpr uint32_t lap_windows(int es) { return kTileElems / (16u / uint32_t(es)); }
+// One-kind launches group such rows too where the tile's windows fit a pass all
+// the same: the eight sub-chunks of a workgroup follow each other, and fewer
+// windows mean fewer workgroups at work.  Boxes of 5, 7 and 9 columns one kind at
+// a time: 131, 141 and 120 us, without the grouping 141, 156 and 126.
+__host__ __device__ inline uint32_t kind_window_group(const TileGeom& g, int es) {
+  return g.nr * windows_per_row(g.nc, es, kSectorBytes) <= lap_windows(es) ? kSectorBytes : window_group(g.nc, es);
+}
 // Sub-chunks of an all-kinds launch past this many of a tile hold nothing of
 // any kind, in windows or (fewer) in vectors.
 __host__ __device__ inline uint32_t sub_used(const TileGeom& g) {
-  const uint32_t w4 = windows_per_row(g.nc, 4), w2 = 2 * windows_per_row(g.nc, 2);
+  const uint32_t w4 = windows_per_row(g.nc, 4, window_group(g.nc, 4));
+  const uint32_t w2 = 2 * windows_per_row(g.nc, 2, window_group(g.nc, 2));
   const uint32_t n = (g.nr * (w4 > w2 ? w4 : w2) + kSubThreads - 1) / kSubThreads;
   return n < kSubPerTile ? n : kSubPerTile;
 }
@@ -161,8 +169,8 @@ __host__ __device__ inline uint32_t sub_used(const TileGeom& g) {
 struct Window {
   int32_t lo, hi;
 };
-__host__ __device__ inline Window row_window(uint32_t w, uint32_t nc, uint64_t to, int es) {
-  const int32_t vw = 16 / es, at = int32_t(w) * vw - int32_t(uint32_t(to) & (window_group(nc, es) - 1)) / es;
+__host__ __device__ inline Window row_window(uint32_t w, uint32_t nc, uint64_t to, int es, uint32_t group) {
+  const int32_t vw = 16 / es, at = int32_t(w) * vw - int32_t(uint32_t(to) & (group - 1)) / es;
   return Window{at > 0 ? at : 0, at + vw < int32_t(nc) ? at + vw : int32_t(nc)};
 }
 

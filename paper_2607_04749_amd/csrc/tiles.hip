@@ -63,8 +63,10 @@ CopyBox make_box(uint64_t a_off, int64_t a_ld, int64_t rows, int64_t cols, uint6
     // 6-layer model's migration), 597 elements 855 -> 812 us, one kind at a
     // time up to 150 -> 100 us (rows of 27 to 113).
     b.tr = rows_by_elems(rows, cols);
-    for (int es : {2, 4})
-      if (!ok(16 / es)) b.tr = std::max(1u, std::min(b.tr, lap_windows(es) / windows_per_row(b.tc, es)));
+    for (int es : {2, 4}) {
+      const uint32_t wpr = windows_per_row(b.tc, es, window_group(b.tc, es));
+      if (!ok(16 / es)) b.tr = std::max(1u, std::min(b.tr, lap_windows(es) / wpr));
+    }
   }
   b.ntc = uint32_t((cols + b.tc - 1) / b.tc);
   b.tile0 = tile0;

@@ -185,7 +185,7 @@ def test_replay_catches_a_planted_geometry_mistake(tmp_path, plant):
 RAGGED = ModelShape(LLAMA, 4, 504, 12, 6, 1362, 5004, 0, 0)
 WINDOW_PLANTS = {
     # the last windows of a row are missing: its end is never copied
-    "a row short of windows": ("/ g * (g / 16u);", "/ g * (g / 16u) - 1;"),
+    "a row short of windows": ("/ group * (group / 16u);", "/ group * (group / 16u) - 1;"),
     # workgroups that still hold windows return at once
     "used sub-chunks rounded down": ("+ kSubThreads - 1) / kSubThreads;", "- 1) / kSubThreads;"),
     # the two-element piece of a row's last window one element on
@@ -193,7 +193,7 @@ WINDOW_PLANTS = {
     # runs of two in the layout of runs of four: sub-chunks copied twice, others never
     "a run order that is no permutation": ("((j & m) / kXcds)", "((j & m) / kXcds / 2)"),
     # windows counted from the wrong unit of the target
-    "windows off their units": ("to) & (window_group(nc, es) - 1)", "to) & (window_group(nc, es) / 2 - 1)"),
+    "windows off their units": ("to) & (group - 1)", "to) & (group / 2 - 1)"),
 }
 
 

@@ -98,13 +98,13 @@ static void walk_vectors(KindWalk& k, const TileGeom& g, uint32_t per, uint32_t 
 }
 
 // The windows of sub-chunk j of a tile, those of a second pass included.
-static void walk_windows(KindWalk& k, const TileGeom& g, uint32_t per, uint32_t j) {
-  const uint32_t vw = 16u / uint32_t(k.es), wpr = windows_per_row(g.nc, k.es), n = g.nr * wpr;
+static void walk_windows(KindWalk& k, const TileGeom& g, uint32_t per, uint32_t j, uint32_t group) {
+  const uint32_t vw = 16u / uint32_t(k.es), wpr = windows_per_row(g.nc, k.es, group), n = g.nr * wpr;
   if (per > kSubThreads) FAIL("a sub-chunk of windows needs more lanes than threads");
   for (uint32_t lane = 0; lane < per; ++lane)
     for (uint32_t i = j * per + lane; i < n; i += lap_windows(k.es)) {
       const uint32_t r = i / wpr;
-      const Window x = row_window(i - r * wpr, g.nc, k.to(r), k.es);
+      const Window x = row_window(i - r * wpr, g.nc, k.to(r), k.es, group);
       if (x.hi <= x.lo) continue;
       const uint64_t at = k.to(r) + uint64_t(x.lo) * k.es;
       const uint32_t m = uint32_t(x.hi - x.lo);
@@ -200,7 +200,8 @@ static void replay_sub(const std::vector<CopyBox>& v, bool pack, bool sectioned,
       writes.clear();
       if (std::max(w.a_ld, w.m_ld) * (g.nr - 1) + uint64_t(g.nc) * es >= (1ull << 31)) FAIL("tile extent over 2^31");
       const bool vk = sub_vectors(b, g, es);
-      if (!vk && g.nr > 1 && g.nr * windows_per_row(g.nc, es) > kTileElems / (16u / uint32_t(es)))
+      const uint32_t group = all ? window_group(g.nc, es) : kind_window_group(g, es);
+      if (!vk && g.nr > 1 && g.nr * windows_per_row(g.nc, es, group) > kTileElems / (16u / uint32_t(es)))
         FAIL("a tile of %u rows of %u elements has windows for a second pass", g.nr, g.nc);
       const uint32_t per = sub_elems / (16u / uint32_t(es));  // vectors or windows per sub-chunk
       // whether every row starts on a line on both sides
@@ -221,7 +222,7 @@ static void replay_sub(const std::vector<CopyBox>& v, bool pack, bool sectioned,
         if (j == 0 && pack && g.last && b.pad && !(all && vectors)) padded = true;
         if (all && !vectors && tile_few(g)) walk_few(w, g);
         else if (vk) walk_vectors(w, g, per, run);
-        else walk_windows(w, g, per, run);
+        else walk_windows(w, g, per, run, group);
       }
       if (pack && g.last && b.pad && !padded) FAIL("the padding after a box is not written");
       if (padded) {

@@ -7,12 +7,12 @@
 #include "copy_geom.hpp"
 using namespace etc;
 
-static int check(uint32_t nc, int es, uint64_t to) {
+static int check(uint32_t nc, int es, uint64_t to, uint32_t group) {
   const int vw = 16 / es;
   std::vector<int> hits(nc, 0);
-  if (nc > 1 && windows_per_row(nc, es) > nc) return 7;
-  for (uint32_t w = 0; w < windows_per_row(nc, es); ++w) {
-    const Window x = row_window(w, nc, to, es);
+  if (nc > 1 && group == window_group(nc, es) && windows_per_row(nc, es, group) > nc) return 7;
+  for (uint32_t w = 0; w < windows_per_row(nc, es, group); ++w) {
+    const Window x = row_window(w, nc, to, es, group);
     if (x.hi <= x.lo) continue;
     if (x.lo < 0 || x.hi > int32_t(nc) || x.hi - x.lo > vw) return 1;
     if (x.hi - x.lo == vw && (to + uint64_t(x.lo) * es) % 16) return 2;
@@ -42,10 +42,11 @@ static int check(uint32_t nc, int es, uint64_t to) {
 // workgroups of an all-kinds launch (in index order or in XCD runs) and of a
 // one-kind launch.
 static int check_tile(uint32_t nr, uint32_t nc, int es) {
-  const uint32_t vw = 16u / uint32_t(es), lap = kTileElems / vw, n = nr * windows_per_row(nc, es);
+  const uint32_t vw = 16u / uint32_t(es), lap = kTileElems / vw;
   const TileGeom g{0, 0, nr, nc, true};
   const uint32_t used = sub_used(g);
   for (int order = 0; order < 3; ++order) {
+    const uint32_t n = nr * windows_per_row(nc, es, order < 2 ? window_group(nc, es) : kind_window_group(g, es));
     std::vector<int> hits(n, 0);
     const uint32_t per = (order < 2 ? kSubElems : kind_sub_elems(es)) / vw;
     if (per > kSubThreads) return 1;
@@ -68,10 +69,11 @@ int main() {
   for (int es : {2, 4})
     for (uint32_t nc : widths)
       for (uint64_t m = 0; m < 256; m += uint64_t(es))
-        if (int e = check(nc, es, 0x7f0000001000ull + m)) {
-          std::printf("row of %u elements of %d bytes at %llu: error %d\n", nc, es, (unsigned long long)m, e);
-          return 1;
-        }
+        for (uint32_t group : {16u, kSectorBytes})
+          if (int e = check(nc, es, 0x7f0000001000ull + m, group)) {
+            std::printf("row of %u elements of %d bytes at %llu: error %d\n", nc, es, (unsigned long long)m, e);
+            return 1;
+          }
   for (int es : {2, 4})
     for (uint32_t nc : widths)
       for (uint32_t nr : {1u, 2u, 3u, kTileElems / nc / 2, kTileElems / nc})
