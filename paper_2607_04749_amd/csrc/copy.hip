@@ -37,11 +37,11 @@
 // consecutive KB per XCD (xcd_run) these became 6.25, 5.85 and 5.7, so boxes
 // off the lines take their sub-chunks in that order; boxes on them do not,
 // which would cost 1.7 %.  Against element-by-element copies on the same
-// buffers, GPU time: a 1.9 B GPT from TP4 to TP6 (rows of 597 elements) 933 ->
-// 798 us; a 6-layer Llama from TP3 to TP2 (rows of 681 and 454) 69.6 -> 62.9;
-// unpacks from TP8 to TP6 with boxes of 7, 27 and 101 columns 67 -> 53, 34 ->
-// 29 and 148 -> 127, and the same steps one kind at a time 236 -> 155, 198 ->
-// 94 and 399 -> 257.
+// buffers, GPU time: a 1.9 B GPT from TP4 to TP6 (rows of 597 elements) 915 ->
+// 797 us; a 6-layer Llama from TP3 to TP2 (rows of 681 and 454) 69.4 -> 63.2;
+// unpacks from TP8 to TP6 with boxes of 7, 27 and 101 columns 66 -> 53, 35 ->
+// 30 and 141 -> 124, and the same steps one kind at a time 239 -> 142, 200 ->
+// 94 and 415 -> 274.
 #include <hip/hip_runtime.h>
 
 #include "copy_desc.hpp"
@@ -95,9 +95,9 @@ struct KindTile {
 };
 
 // Window w of a row of nc elements, as one vector or up to three pieces.  All
-// of a wavefront's loads are issued before any store: most wavefronts hold an
-// end of some row, and a second load after the first store would double their
-// time.  (Rows inside one 16-byte unit went element by element, a load and a
+// of a wavefront's loads of a kind are issued before any store of that kind:
+// most wavefronts hold an end of some row, and a second load after the first
+// store would double their time.  (Rows inside one 16-byte unit went element by element, a load and a
 // store in turn: tiny boxes of 5-wide rows 4 to 5 % slower than in pieces.)
 template <int kEs>
 __device__ __forceinline__ void copy_window(const char* src, char* dst, uint32_t w, uint32_t nc, uint32_t group) {
@@ -119,7 +119,8 @@ __device__ __forceinline__ void copy_window(const char* src, char* dst, uint32_t
     if (p.p2) __builtin_memcpy(&v2, src + p.e2 * kEs, 2 * kEs);
     if (p.p1) __builtin_memcpy(&v1, src + p.e1 * kEs, kEs);
   }
-  // one wait for all of them: waits of their own would also wait for stores
+  // one wait for all of them: vmcnt counts stores too, so waits of their own
+  // would wait for stores (as this one does for those of the kind before)
   __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt 0
   if (m == vw) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst));
   if (m < vw) {
@@ -182,7 +183,7 @@ __device__ __forceinline__ void copy_sub_any(const KindTile<kPack, kEs>& k, cons
 // All four kinds of a tile of at most one element per lane: the loads of all
 // kinds before any store, and no windows to work out.  In windows such tiles took
 // longer than element by element: 400 layers of hidden 6 and 10, unpack 196 and
-// 200 us (180 and 189 by elements), 137 and 150 this way.
+// 200 us (180 and 189 by elements), 128 and 142 this way.
 template <bool kPack>
 __device__ __forceinline__ void copy_few(const CopyArgs& a, const CopyBox& b, char* mbase, const TileGeom& g) {
   const KindTile<kPack, 2> k0(a, b, mbase, g, 0);
